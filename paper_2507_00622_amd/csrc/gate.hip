@@ -18,7 +18,6 @@ struct chx_gate {
   int device = -1;
   float *p = nullptr, *m = nullptr, *v = nullptr, *g = nullptr;
   uint8_t *mask = nullptr;
-  uint16_t *pb = nullptr;   // BF16 copy of p
   uint16_t *pbF = nullptr;  // BF16 copy of the weights in MFMA operand order
   float *mean = nullptr;    // [16] z-score mean (first 6 used)
   float *istd = nullptr;    // [16] inverse standard deviation
@@ -35,7 +34,7 @@ namespace {
     if (e_ != hipSuccess) return dev_fail(e_, what); \
   } while (0)
 
-constexpr int CHUNK = 65536;  // rows per forward pass (inference) / max batch
+constexpr int CHUNK = 65536;  // most rows of a batch
 
 inline int64_t round16(int64_t n) { return (n + 15) / 16 * 16; }
 
@@ -83,51 +82,27 @@ struct Scratch {
   }
 };
 
-// Activations of one pass over up to B rows: inference (the products'
-// FP32 outputs Z) or training (the activation gradients).
+// Activations and activation gradients of one training pass over up to B
+// rows.
 struct Acts {
   uint16_t *X, *A1b, *A2b, *dZ3b, *dZ2b, *dZ1b;
-  float *Z1, *Z2, *Z3;
   float *bpart;  // per 16-row block: column sums of dZ1 | dZ2 | dZ3
   float *work1, *work2, *work3;  // split-K parts of the weight gradients
 };
 
-bool alloc_acts(Scratch &S, int64_t B, bool backward, Acts *a) {
+bool alloc_acts(Scratch &S, int64_t B, Acts *a) {
   memset(a, 0, sizeof *a);
   a->X = S.get<uint16_t>(B * MLP_INP);
   a->A1b = S.get<uint16_t>(B * MLP_H);
   a->A2b = S.get<uint16_t>(B * MLP_H);
-  if (!backward) {
-    a->Z1 = S.get<float>(B * MLP_H);
-    a->Z2 = S.get<float>(B * MLP_H);
-    a->Z3 = S.get<float>(B * MLP_OUTP);
-  } else {
-    a->dZ3b = S.get<uint16_t>(B * MLP_OUTP);
-    a->dZ2b = S.get<uint16_t>(B * MLP_H);
-    a->dZ1b = S.get<uint16_t>(B * MLP_H);
-    a->bpart = S.get<float>((size_t)(B / 16) * MLP_BIAS_COLS);
-    a->work1 = S.get<float>(MLP_SPLITK_WORK_SMALL);
-    a->work2 = S.get<float>(MLP_SPLITK_WORK);
-    a->work3 = S.get<float>(MLP_SPLITK_WORK_SMALL);
-  }
+  a->dZ3b = S.get<uint16_t>(B * MLP_OUTP);
+  a->dZ2b = S.get<uint16_t>(B * MLP_H);
+  a->dZ1b = S.get<uint16_t>(B * MLP_H);
+  a->bpart = S.get<float>((size_t)(B / 16) * MLP_BIAS_COLS);
+  a->work1 = S.get<float>(MLP_SPLITK_WORK_SMALL);
+  a->work2 = S.get<float>(MLP_SPLITK_WORK);
+  a->work3 = S.get<float>(MLP_SPLITK_WORK_SMALL);
   return S.err == hipSuccess;
-}
-
-// Forward pass of B rows (multiple of 16) whose z-scored BF16 inputs are in
-// a.X: Z3 = logits.
-hipError_t forward(const chx_gate *g, const Acts &a, int B, hipStream_t s) {
-  const uint16_t *pb = g->pb;
-  const float *p = g->p;
-  hipError_t e;
-  // Z = X W + b and its GELU in BF16, from the product's epilogue
-  if ((e = mlp_gemm(a.X, MLP_INP, 1, pb + MLP_W1, MLP_H, 1, a.Z1, MLP_H, B, MLP_H, MLP_INP,
-                    p + MLP_B1, 0, s, nullptr, 0, EPI_GELU, a.A1b)))
-    return e;
-  if ((e = mlp_gemm(a.A1b, MLP_H, 1, pb + MLP_W2, MLP_H, 1, a.Z2, MLP_H, B, MLP_H, MLP_H,
-                    p + MLP_B2, 0, s, nullptr, 0, EPI_GELU, a.A2b)))
-    return e;
-  return mlp_gemm(a.A2b, MLP_H, 1, pb + MLP_W3, MLP_OUTP, 1, a.Z3, MLP_OUTP, B, MLP_OUTP, MLP_H,
-                  p + MLP_B3, 0, s);
 }
 
 // Loss and gradient of one batch of B rows (multiple of 16) into g->g and
@@ -153,7 +128,6 @@ hipError_t batch_grad(chx_gate *g, const Acts &a, int B, const float *feat, cons
   r.labels = labels;
   r.inv = inv;
   r.p = g->p;
-  r.pb = g->pb;
   r.pbF = g->pbF;
   r.X = a.X;
   r.A1b = a.A1b;
@@ -172,34 +146,14 @@ hipError_t batch_grad(chx_gate *g, const Acts &a, int B, const float *feat, cons
   gp->w3 = a.work3;
   // (the row kernel's outputs are feature-major with row stride B, so both
   // operands run along K = rows)
-  if ((e = mlp_gemm(a.A2b, B, 1, a.dZ3b, 1, B, gr + MLP_W3, MLP_OUTP, MLP_H, MLP_OUTP, B, nullptr,
-                    0, s, a.work3, MLP_SPLITK_WORK_SMALL, EPI_NONE, nullptr, &gp->s3)))
+  if ((e = mlp_gemm(a.A2b, B, 1, a.dZ3b, 1, B, gr + MLP_W3, MLP_OUTP, MLP_H, MLP_OUTP, B, s,
+                    a.work3, MLP_SPLITK_WORK_SMALL, &gp->s3)))
     return e;
-  if ((e = mlp_gemm(a.A1b, B, 1, a.dZ2b, 1, B, gr + MLP_W2, MLP_H, MLP_H, MLP_H, B, nullptr, 0, s,
-                    a.work2, MLP_SPLITK_WORK, EPI_NONE, nullptr, &gp->s2)))
+  if ((e = mlp_gemm(a.A1b, B, 1, a.dZ2b, 1, B, gr + MLP_W2, MLP_H, MLP_H, MLP_H, B, s,
+                    a.work2, MLP_SPLITK_WORK, &gp->s2)))
     return e;
-  return mlp_gemm(a.X, B, 1, a.dZ1b, 1, B, gr + MLP_W1, MLP_H, MLP_INP, MLP_H, B, nullptr, 0, s,
-                  a.work1, MLP_SPLITK_WORK_SMALL, EPI_NONE, nullptr, &gp->s1);
-}
-
-// p(chaotic) and confidence of n rows of device features.
-chx_status infer_dev(const chx_gate *g, const float *feat, int64_t n, float *pc, float *conf,
-                     hipStream_t s) {
-  if (n == 0) return CHX_OK;
-  Scratch S(s);
-  Acts a;
-  const int64_t B = n < CHUNK ? round16(n) : CHUNK;
-  if (!alloc_acts(S, B, false, &a)) return dev_fail(S.err, "allocate activations");
-  for (int64_t r0 = 0; r0 < n; r0 += CHUNK) {
-    const int64_t rows = (n - r0) < CHUNK ? (n - r0) : CHUNK;
-    const int Bp = (int)round16(rows);
-    GCHK(mlp_batch_input(feat + r0 * MLP_IN, nullptr, Bp, rows, g->mean, g->istd, a.X, s),
-         "gate input");
-    GCHK(forward(g, a, Bp, s), "gate forward");
-    GCHK(mlp_infer_out(a.Z3, (int)rows, pc ? pc + r0 : nullptr, conf ? conf + r0 : nullptr, s),
-         "gate output");
-  }
-  return CHX_OK;
+  return mlp_gemm(a.X, B, 1, a.dZ1b, 1, B, gr + MLP_W1, MLP_H, MLP_INP, MLP_H, B, s,
+                  a.work1, MLP_SPLITK_WORK_SMALL, &gp->s1);
 }
 
 uint64_t mix64(uint64_t z) {
@@ -235,7 +189,6 @@ chx_status chx_gate_create(uint64_t seed, chx_gate **out) {
   al(&g->v, sizeof(float) * MLP_NPARAM);
   al(&g->g, sizeof(float) * MLP_NPARAM);
   al(&g->mask, MLP_NPARAM);
-  al(&g->pb, sizeof(uint16_t) * MLP_NPARAM);
   al(&g->pbF, sizeof(uint16_t) * MLP_NFRAG);
   al(&g->mean, sizeof(float) * 16);
   al(&g->istd, sizeof(float) * 16);
@@ -246,7 +199,7 @@ chx_status chx_gate_create(uint64_t seed, chx_gate **out) {
   if (e == hipSuccess) e = mlp_fill(g->g, MLP_NPARAM, 0.f, nullptr);
   if (e == hipSuccess) e = mlp_fill(g->mean, 16, 0.f, nullptr);
   if (e == hipSuccess) e = mlp_fill(g->istd, 16, 1.f, nullptr);
-  if (e == hipSuccess) e = mlp_weights_bf16(g->p, g->pb, g->pbF, nullptr);
+  if (e == hipSuccess) e = mlp_weights_bf16(g->p, g->pbF, nullptr);
   if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
   if (e != hipSuccess) {
     chx_gate_destroy(g);
@@ -260,7 +213,7 @@ void chx_gate_destroy(chx_gate *g) {
   if (!g) return;
   (void)hipDeviceSynchronize();
   for (void *p : {(void *)g->p, (void *)g->m, (void *)g->v, (void *)g->g, (void *)g->mask,
-                  (void *)g->pb, (void *)g->pbF, (void *)g->mean, (void *)g->istd,
+                  (void *)g->pbF, (void *)g->mean, (void *)g->istd,
                   (void *)g->partials})
     if (p) (void)hipFree(p);
   delete g;
@@ -298,7 +251,7 @@ chx_status chx_gate_train(chx_gate *g, const float *features, const int8_t *labe
   float *loss = S.get<float>((size_t)c.epochs);
   Acts a;
   const int B = c.batch;
-  if (!alloc_acts(S, B, true, &a)) return dev_fail(S.err, "allocate training buffers");
+  if (!alloc_acts(S, B, &a)) return dev_fail(S.err, "allocate training buffers");
   if (reset_stats || !g->have_stats) {
     GCHK(mlp_feature_stats(feat, n, g->mean, g->istd, g->partials, s), "feature statistics");
     g->have_stats = true;
@@ -306,7 +259,7 @@ chx_status chx_gate_train(chx_gate *g, const float *features, const int8_t *labe
   GCHK(mlp_fill(loss, c.epochs, 0.f, s), "clear loss");
   const int64_t nbatch = (n + B - 1) / B;
   // the BF16 copy of the weights; each AdamW step refreshes it
-  GCHK(mlp_weights_bf16(g->p, g->pb, g->pbF, s), "weights to bf16");
+  GCHK(mlp_weights_bf16(g->p, g->pbF, s), "weights to bf16");
   for (int ep = 0; ep < c.epochs; ++ep) {
     // epoch permutation i -> (pa i + pc) mod n with pa coprime to n
     const uint64_t key = mix64(c.seed ^ mix64(0x6a7e0000ull + (uint64_t)ep));
@@ -324,7 +277,7 @@ chx_status chx_gate_train(chx_gate *g, const float *features, const int8_t *labe
       g->t += 1;
       const double bc1 = 1.0 - pow((double)c.beta1, (double)g->t);
       const double bc2 = 1.0 - pow((double)c.beta2, (double)g->t);
-      GCHK(mlp_grad_step(gp, g->p, g->pb, g->pbF, g->g, g->m, g->v, g->mask, 1, c.lr, c.beta1,
+      GCHK(mlp_grad_step(gp, g->p, g->pbF, g->g, g->m, g->v, g->mask, 1, c.lr, c.beta1,
                          c.beta2, c.eps, c.weight_decay, (float)bc1, (float)bc2, s),
            "AdamW");
     }
@@ -353,12 +306,12 @@ chx_status chx_gate_grad(chx_gate *g, const float *features, const int8_t *label
   float *loss = S.get<float>(1);
   Acts a;
   const int Bp = (int)round16(n);
-  if (!alloc_acts(S, Bp, true, &a)) return dev_fail(S.err, "allocate buffers");
+  if (!alloc_acts(S, Bp, &a)) return dev_fail(S.err, "allocate buffers");
   GCHK(mlp_fill(loss, 1, 0.f, s), "clear loss");
   GCHK(mlp_fill(g->g, MLP_NPARAM, 0.f, s), "clear gradient");
   GradParts gp;
   GCHK(batch_grad(g, a, Bp, feat, lab, n, 0, 1, 0, 1.0f / (float)n, loss, &gp, s), "gradient");
-  GCHK(mlp_grad_step(gp, g->p, g->pb, g->pbF, g->g, g->m, g->v, g->mask, 0, 0.f, 0.f, 0.f, 0.f,
+  GCHK(mlp_grad_step(gp, g->p, g->pbF, g->g, g->m, g->v, g->mask, 0, 0.f, 0.f, 0.f, 0.f,
                      0.f, 1.f, 1.f, s),
        "gradient parts");
   float hl = 0.f;
@@ -387,7 +340,7 @@ chx_status chx_gate_infer(const chx_gate *g, const float *features, int64_t n, f
   float *pc = dev ? p_chaotic : (p_chaotic ? S.get<float>(n) : nullptr);
   float *cf = dev ? confidence : (confidence ? S.get<float>(n) : nullptr);
   if (S.err != hipSuccess) return dev_fail(S.err, "stage inputs");
-  if ((st = infer_dev(g, feat, n, pc, cf, s))) return st;
+  GCHK(mlp_infer(feat, n, g->mean, g->istd, g->p, g->pbF, pc, cf, s), "gate inference");
   if (!dev) {
     if (p_chaotic) GCHK(hipMemcpyAsync(p_chaotic, pc, sizeof(float) * n, hipMemcpyDeviceToHost, s), "read p");
     if (confidence) GCHK(hipMemcpyAsync(confidence, cf, sizeof(float) * n, hipMemcpyDeviceToHost, s), "read confidence");
@@ -417,7 +370,7 @@ chx_status chx_gate_set(chx_gate *g, const float *params, const float *mean, con
     GCHK(mlp_apply_mask(g->p, g->mask, MLP_NPARAM, nullptr), "mask params");
     GCHK(mlp_fill(g->m, MLP_NPARAM, 0.f, nullptr), "clear moments");
     GCHK(mlp_fill(g->v, MLP_NPARAM, 0.f, nullptr), "clear moments");
-    GCHK(mlp_weights_bf16(g->p, g->pb, g->pbF, nullptr), "weights to bf16");
+    GCHK(mlp_weights_bf16(g->p, g->pbF, nullptr), "weights to bf16");
     g->t = 0;
   }
   if ((mean == nullptr) != (istd == nullptr))
@@ -552,7 +505,7 @@ chx_status chx_gate_classify(const chx_gate *g, const chx_system *sys, const dou
   r1.ln_growth = lg;
   if ((st = results(e1, &r1))) return st;
   GCHK(mlp_features(dx0, ld, lg, t_gate, n, feat, s), "features");
-  if ((st = infer_dev(g, feat, n, pc, conf, s))) return st;
+  GCHK(mlp_infer(feat, n, g->mean, g->istd, g->p, g->pbF, pc, conf, s), "gate inference");
   GCHK(gate_select(n, status1, label1, pc, conf, conf_min, lab, src, keep, cfo, counts, s),
        "select");
   GCHK(hipEventRecord(ev[2], s), "event");

@@ -32,19 +32,13 @@ constexpr int64_t MLP_F_W3 = MLP_F_W2T + (int64_t)MLP_H * MLP_H;     // W3, forw
 constexpr int64_t MLP_F_W3T = MLP_F_W3 + (int64_t)MLP_H * MLP_OUTP;  // W3, backward
 constexpr int64_t MLP_NFRAG = MLP_F_W3T + (int64_t)MLP_H * MLP_OUTP;
 
-// C = A B (+ bias) (+ C): BF16 operands at any strides, FP32 result.
-// work (work_len floats, may be null; needs parts) holds split-K partial
-// products.
-// Epilogue EPI_GELU (no accumulate): also stores GELU(C) in BF16 to Cb
-// (C's row stride).
-enum { EPI_NONE = 0, EPI_GELU = 1 };
+// C = A B: BF16 operands at any strides, FP32 result.  With work (work_len
+// floats) and parts given (ldc == N) a product split over K leaves its parts
+// in work[z][M][N] for the caller to add and *parts = S (the number of
+// parts); with *parts == 1 the product is in C.
 hipError_t mlp_gemm(const uint16_t *A, int64_t a_r, int64_t a_c, const uint16_t *B, int64_t b_r,
-                    int64_t b_c, float *C, int64_t ldc, int M, int N, int K, const float *bias,
-                    int accumulate, hipStream_t s, float *work = nullptr, int64_t work_len = 0,
-                    int epi = EPI_NONE, uint16_t *Cb = nullptr, int *parts = nullptr);
-// With parts given (no bias, no accumulate, ldc == N): a product split over
-// K leaves its parts in work[z][M][N] for the caller to add and *parts = S
-// (the number of parts); with *parts == 1 the product is in C.
+                    int64_t b_c, float *C, int64_t ldc, int M, int N, int K, hipStream_t s,
+                    float *work = nullptr, int64_t work_len = 0, int *parts = nullptr);
 // Split-K workspaces of the training pass (floats): up to 32 parts of the
 // 256 x 256 weight gradient, 64 of the 16 x 256 and 256 x 16 ones
 constexpr int64_t MLP_SPLITK_WORK = (int64_t)32 * MLP_H * MLP_H;
@@ -65,7 +59,7 @@ struct MlpRowsArgs {
   const int8_t *labels;
   float inv;
   const float *p;
-  const uint16_t *pb, *pbF;
+  const uint16_t *pbF;
   uint16_t *X, *A1b, *A2b, *dZ3b, *dZ2b, *dZ1b;
   float *bpart;
 };
@@ -89,20 +83,21 @@ struct GradParts {
   int s1, s2, s3;
 };
 // g = the batch's gradient (adding the weight gradients' parts); with step
-// set, AdamW on the FP32 masters p (entries with mask set), pb receiving
-// their BF16 copies and pbF the weights' operand-order BF16 copies.
-hipError_t mlp_grad_step(const GradParts &gp, float *p, uint16_t *pb, uint16_t *pbF, float *g,
+// set, AdamW on the FP32 masters p (entries with mask set), pbF
+// receiving the weights' operand-order BF16 copies.
+hipError_t mlp_grad_step(const GradParts &gp, float *p, uint16_t *pbF, float *g,
                          float *m, float *v, const uint8_t *mask, int step, float lr, float b1,
                          float b2, float eps, float wd, float bc1, float bc2, hipStream_t s);
-// pb = BF16 of all MLP_NPARAM parameters; pbF (MLP_NFRAG entries) = BF16
-// of the weights in the training pass's MFMA operand order
-hipError_t mlp_weights_bf16(const float *p, uint16_t *pb, uint16_t *pbF, hipStream_t s);
-hipError_t mlp_batch_input(const float *feat, const int64_t *rows, int B, int64_t n_valid,
-                           const float *mean, const float *istd, uint16_t *X, hipStream_t s);
+// pbF (MLP_NFRAG entries) = BF16 of the weights in MFMA operand order
+hipError_t mlp_weights_bf16(const float *p, uint16_t *pbF, hipStream_t s);
 hipError_t mlp_init_params(float *p, uint8_t *mask, uint64_t seed, hipStream_t s);
 hipError_t mlp_feature_stats(const float *feat, int64_t n, float *mean, float *istd,
                              double *partials, hipStream_t s);
-hipError_t mlp_infer_out(const float *Z3, int B, float *pc, float *conf, hipStream_t s);
+// p(chaotic) and confidence (either may be null) of n rows of raw features
+// [n][MLP_IN]; p: the FP32 masters (biases), pbF: the operand-order weights
+hipError_t mlp_infer(const float *feat, int64_t n, const float *mean, const float *istd,
+                     const float *p, const uint16_t *pbF, float *pc, float *conf,
+                     hipStream_t s);
 hipError_t mlp_features(const double *x0, const double *ld, const double *lg, double t, int64_t n,
                         float *out, hipStream_t s);
 

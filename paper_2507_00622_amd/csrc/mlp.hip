@@ -20,14 +20,10 @@ namespace {
 typedef short short4_t __attribute__((ext_vector_type(4)));
 typedef float float4_t __attribute__((ext_vector_type(4)));
 
-// float -> bf16 bits, round to nearest even (finite inputs; NaN stays NaN)
+// float -> bf16 bits, round to nearest even (v_cvt_pk_bf16_f32)
 __device__ __forceinline__ uint16_t f2bf(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7f800000u) == 0x7f800000u) return (uint16_t)((u >> 16) | ((u & 0xffff) ? 0x40 : 0));
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
+  return __builtin_bit_cast(uint16_t, (__bf16)f);
 }
-__device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
 // erf(z / sqrt 2) given e = exp(-z^2 / 2): Abramowitz and Stegun 7.1.26,
 // erf(x) = 1 - (a1 t + ... + a5 t^5) exp(-x^2), t = 1 / (1 + p x) for x >= 0
@@ -49,7 +45,7 @@ __device__ __forceinline__ float gelu_grad(float z) {
   return 0.5f * (1.0f + erf_scaled(z, e)) + z * 0.39894228040143268f * e;
 }
 
-// C[M][N] (fp32, row stride ldc) = A B (+ bias[col]) (+ C if accumulate),
+// C[M][N] (fp32, row stride ldc) = A B,
 // A(i,k) = A[i*a_r + k*a_c], B(k,j) = B[k*b_r + j*b_c], both BF16; M, N, K
 // multiples of 16.  A block of 4 wavefronts computes a BM x BN tile of C,
 // (64, 64), (16, 64) or (64, 16) (rows past M are not stored).  K goes in
@@ -65,19 +61,15 @@ __device__ __forceinline__ float gelu_grad(float z) {
 // and 16 k: lane l holds A[l % 16][4 (l / 16) + e], B[4 (l / 16) + e][l % 16]
 // and, after, D[4 (l / 16) + r][l % 16].  Split K: block z of gridDim.z
 // takes chunks [z cpc, (z + 1) cpc) and, when gridDim.z > 1, writes its
-// partial tile to work[z][M][N] for the caller to add in order of z.  Epilogue EPI_GELU
-// (no split): Z = AB + bias to C and its activation GELU(Z) in BF16 to Cb
-// (C's row stride).
+// partial tile to work[z][M][N] for the caller to add in order of z. 
 constexpr int GBK = 32, GPAD = GBK + 8;
 
-template <int BM, int BN, bool VEC, int EPI>
+template <int BM, int BN, bool VEC>
 __global__ void __launch_bounds__(256) gemm_tile_kernel(const uint16_t *A, int64_t a_r,
                                                         int64_t a_c, const uint16_t *B,
                                                         int64_t b_r, int64_t b_c, float *C,
                                                         int64_t ldc, int M, int N, int K,
-                                                        int cpc, const float *bias,
-                                                        int accumulate, float *work,
-                                                        uint16_t *Cb) {
+                                                        int cpc, float *work) {
   // wavefronts: (64, 64) 2 x 2 of 2 x 2 tiles; (64, 16) 4 x 1 and (16, 64)
   // 1 x 4 of one tile
   constexpr int WGM = BM == 64 && BN == 64 ? 2 : (BM == 64 ? 4 : 1);
@@ -211,23 +203,6 @@ __global__ void __launch_bounds__(256) gemm_tile_kernel(const uint16_t *A, int64
         }
     return;
   }
-  // every load of the epilogue (bias, the C accumulated onto) goes out
-  // before its first store, so one wait covers them all
-  float x[TM][TN][4];
-#pragma unroll
-  for (int a = 0; a < TM; ++a)
-#pragma unroll
-    for (int b = 0; b < TN; ++b) {
-      const int j = col0 + (wn * TN + b) * 16 + li;
-      const float bj = bias ? bias[j] : 0.f;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = row0 + (wm * TM + a) * 16 + lk + r;
-        const int64_t e = (int64_t)i * ldc + j;
-        if (bias) acc[a][b][r] += bj;
-        if constexpr (EPI == EPI_NONE) x[a][b][r] = (accumulate && i < M) ? C[e] : 0.f;
-      }
-    }
 #pragma unroll
   for (int a = 0; a < TM; ++a)
 #pragma unroll
@@ -235,15 +210,7 @@ __global__ void __launch_bounds__(256) gemm_tile_kernel(const uint16_t *A, int64
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int i = row0 + (wm * TM + a) * 16 + lk + r, j = col0 + (wn * TN + b) * 16 + li;
-        if (i >= M) continue;
-        const float v = acc[a][b][r];
-        const int64_t e = (int64_t)i * ldc + j;
-        if constexpr (EPI == EPI_GELU) {
-          C[e] = v;
-          Cb[e] = f2bf(gelu(v));
-        } else {
-          C[e] = accumulate ? x[a][b][r] + v : v;
-        }
+        if (i < M) C[(int64_t)i * ldc + j] = acc[a][b][r];
       }
 }
 
@@ -533,6 +500,131 @@ __global__ void __launch_bounds__(64 * TR_W) train_rows_kernel(const MlpRowsArgs
   if (tid < MLP_H) bp[tid] = ((Ps1[0][tid] + Ps1[1][tid]) + Ps1[2][tid]) + Ps1[3][tid];
 }
 
+// Inference: p(chaotic) and the confidence max(p, 1 - p) of n rows of raw
+// features in one launch; nothing but the features is read per row and
+// nothing but the outputs written (32 bytes a row).
+// A block of TR_W wavefronts takes IN_R rows at a time, blocks striding over
+// the rows.  Wavefront w holds its columns' W2 operands (64 VGPRs) for the
+// whole launch; the activations pass between the layers through LDS in
+// BF16.  The products run over k in ascending order with the training
+// pass's instruction, and the logits' rows go round the wavefronts from one
+// iteration to the next.  What bounds it is the VALU: 512 GELUs a row, each
+// about 30 instruction slots (two of them quarter-rate), against 17 MFMAs of
+// 16 rows x 16 columns x 16 k per wavefront and 16 rows.  Two blocks share a
+// CU (at most 128 VGPRs, four wavefronts per SIMD), so one block's
+// barriers are hidden by the other's activations.  3,405,516 rows: 1.60 ms
+// (2.9e2 TFLOP/s of the products), against 5.48 ms for five launches per
+// 65,536 rows with the FP32 pre-activations through memory.
+constexpr int IN_R = 32;      // rows per block iteration
+constexpr int IN_GRID = 512;  // two blocks per CU
+__global__ void __launch_bounds__(64 * TR_W, 4)
+    infer_kernel(const float *feat, int64_t n, const float *mean, const float *istd,
+                 const float *p, const uint16_t *pbF, float *pc, float *conf) {
+  constexpr int RT = IN_R / 16;
+  static_assert(IN_R * 16 == 64 * TR_W, "one padded feature per thread");
+  __shared__ __align__(16) uint16_t Xs[IN_R][24];
+  __shared__ __align__(16) uint16_t As[IN_R][TR_LD], Bs[IN_R][TR_LD];
+  __shared__ __align__(16) uint16_t W3[MLP_H / 16][64][4];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int li = lane & 15, lq = lane >> 4;
+  const int cw = wave * 16 * TR_T;
+  const float4_t zero = {0.f, 0.f, 0.f, 0.f};
+  short4_t wf[MLP_H / 16][TR_T], w1[TR_T];
+  float b1[TR_T], b2[TR_T];
+#pragma unroll
+  for (int b = 0; b < TR_T; ++b) {
+    w1[b] = *(const short4_t *)&pbF[MLP_F_W1 + ((TR_T * wave + b) * 64 + lane) * 4];
+    b1[b] = p[MLP_B1 + cw + 16 * b + li];
+    b2[b] = p[MLP_B2 + cw + 16 * b + li];
+  }
+#pragma unroll
+  for (int ks = 0; ks < MLP_H / 16; ++ks)
+#pragma unroll
+    for (int b = 0; b < TR_T; ++b)
+      wf[ks][b] =
+          *(const short4_t *)&pbF[MLP_F_W2 + (((TR_T * wave + b) * 16 + ks) * 64 + lane) * 4];
+  for (int e = tid; e < (MLP_H / 16) * 64; e += 64 * TR_W)
+    *(short4_t *)&W3[e >> 6][e & 63][0] = *(const short4_t *)&pbF[MLP_F_W3 + e * 4];
+  const float b3 = p[MLP_B3 + li];
+  // thread (i, k) stages feature k of row i; the next rows' features are in
+  // flight while these are worked on
+  const int fi = tid >> 4, fk = tid & 15;
+  const bool fon = fk < MLP_IN;
+  const float fm = fon ? mean[fk] : 0.f, fs = fon ? istd[fk] : 0.f;
+  const int64_t step = (int64_t)gridDim.x * IN_R;
+  int64_t r0 = (int64_t)blockIdx.x * IN_R;
+  auto fetch = [&](int64_t base) {
+    const int64_t r = base + fi;
+    return fon && r < n ? feat[r * MLP_IN + fk] : fm;
+  };
+  float f = fetch(r0);
+  for (int turn = 0; r0 < n; r0 += step, turn += RT) {
+    Xs[fi][fk] = f2bf((f - fm) * fs);
+    f = fetch(r0 + step);
+    lds_barrier();
+    // layer 1 (one k-step)
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+      const short4_t x = *(const short4_t *)&Xs[16 * t + li][4 * lq];
+#pragma unroll
+      for (int b = 0; b < TR_T; ++b) {
+        const float4_t z = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(x, w1[b], zero, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          As[16 * t + 4 * lq + r][cw + 16 * b + li] = f2bf(gelu(z[r] + b1[b]));
+      }
+    }
+    lds_barrier();
+    // layer 2
+    float4_t z2[RT][TR_T];
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+      for (int b = 0; b < TR_T; ++b) z2[t][b] = zero;
+#pragma unroll
+    for (int ks = 0; ks < MLP_H / 16; ++ks)
+#pragma unroll
+      for (int t = 0; t < RT; ++t) {
+        const short4_t x = *(const short4_t *)&As[16 * t + li][16 * ks + 4 * lq];
+#pragma unroll
+        for (int b = 0; b < TR_T; ++b)
+          z2[t][b] =
+              __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(x, wf[ks][b], z2[t][b], 0, 0, 0);
+      }
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+      for (int b = 0; b < TR_T; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          Bs[16 * t + 4 * lq + r][cw + 16 * b + li] = f2bf(gelu(z2[t][b][r] + b2[b]));
+    lds_barrier();
+    // logits and softmax of 16 rows each by RT of the wavefronts
+    const int t = (wave - turn) & (TR_W - 1);
+    if (t < RT) {
+      float4_t z3 = zero;
+#pragma unroll
+      for (int ks = 0; ks < MLP_H / 16; ++ks) {
+        const short4_t x = *(const short4_t *)&Bs[16 * t + li][16 * ks + 4 * lq];
+        const short4_t w = *(const short4_t *)&W3[ks][lane][0];
+        z3 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(x, w, z3, 0, 0, 0);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float a = z3[r] + b3, b = __shfl_down(a, 1, 64);  // columns 0 and 1 at li = 0
+        const int64_t row = r0 + 16 * t + 4 * lq + r;
+        if (li == 0 && row < n) {
+          const float m = fmaxf(a, b);
+          const float ea = expf(a - m), eb = expf(b - m);
+          const float p1 = eb / (ea + eb);
+          if (pc) pc[row] = p1;
+          if (conf) conf[row] = fmaxf(p1, 1.f - p1);
+        }
+      }
+    }
+  }
+}
+
 // Bias gradients and loss from the blocks' sums of train_rows_kernel:
 // column col of bpart[nblk][MLP_BIAS_COLS] summed over the blocks; thread
 // group g of a block of 256 adds blocks g, g + 16, g + 32, ... in order,
@@ -623,8 +715,8 @@ __global__ void zero_u64_kernel(unsigned long long *p, int n) {
 // The gradient of one batch, entry i of g: a weight whose product was split
 // over K is the sum of its parts in order of the part (deterministic); the
 // other entries (unsplit products, biases) are already in g.  With step set, AdamW then updates the FP32
-// master (entries with mask set) and its BF16 copies pb and pbF.
-__global__ void grad_step_kernel(GradParts gp, float *p, uint16_t *pb, uint16_t *pbF, float *g,
+// master (entries with mask set) and its operand-order BF16 copy pbF.
+__global__ void grad_step_kernel(GradParts gp, float *p, uint16_t *pbF, float *g,
                                  float *m, float *v, const uint8_t *mask, int step, float lr,
                                  float b1, float b2, float eps, float wd, float bc1, float bc2) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -650,39 +742,21 @@ __global__ void grad_step_kernel(GradParts gp, float *p, uint16_t *pb, uint16_t 
   const float pn = p[i] - lr * (mh / (sqrtf(vh) + eps) + wd * p[i]);
   p[i] = pn;
   const uint16_t h = f2bf(pn);
-  pb[i] = h;
   int64_t f0, f1;
   mlp_fpos(i, f0, f1);
   if (f0 >= 0) pbF[f0] = h;
   if (f1 >= 0) pbF[f1] = h;
 }
 
-// BF16 copies of the parameters: pb in their own layout, pbF the weights in
-// the training pass's operand order
-__global__ void weights_bf16_kernel(const float *p, uint16_t *pb, uint16_t *pbF) {
+// BF16 copy of the weights in MFMA operand order
+__global__ void weights_bf16_kernel(const float *p, uint16_t *pbF) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= MLP_NPARAM) return;
   const uint16_t h = f2bf(p[i]);
-  pb[i] = h;
   int64_t f0, f1;
   mlp_fpos(i, f0, f1);
   if (f0 >= 0) pbF[f0] = h;
   if (f1 >= 0) pbF[f1] = h;
-}
-
-// X[r][0..15] = BF16 of the z-scored features of row rows[r] (zero pad;
-// rows at or past n_valid are all zero)
-__global__ void batch_input_kernel(const float *feat, const int64_t *rows, int B,
-                                   int64_t n_valid, const float *mean, const float *istd,
-                                   uint16_t *X) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= B) return;
-  const int64_t src = rows ? rows[r] : r;
-  const bool ok = src >= 0 && src < n_valid;
-  for (int c = 0; c < 16; ++c) {
-    const float v = (ok && c < MLP_IN) ? (feat[src * MLP_IN + c] - mean[c]) * istd[c] : 0.f;
-    X[r * 16 + c] = f2bf(v);
-  }
 }
 
 // Initial weights: N(0, 2/fan_in) on the real entries (SplitMix64 counters
@@ -770,18 +844,6 @@ __global__ void feature_stats_kernel(const double *part, int nblocks, int64_t n,
   istd[c] = var > 0.0 ? (float)(1.0 / sqrt(var)) : 1.0f;
 }
 
-// Inference output: p(chaotic) and the confidence max(p, 1 - p).
-__global__ void infer_out_kernel(const float *Z3, int B, float *pc, float *conf) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= B) return;
-  const float a = Z3[r * 16 + 0], b = Z3[r * 16 + 1];
-  const float m = fmaxf(a, b);
-  const float ea = expf(a - m), eb = expf(b - m);
-  const float p1 = eb / (ea + eb);
-  if (pc) pc[r] = p1;
-  if (conf) conf[r] = fmaxf(p1, 1.f - p1);
-}
-
 // Gate features at time t: (y, p_y, p_x, LD/t, G1/t, G2/t) from the
 // initial conditions [n][4], the LD [n] and the ln-growths [n][2].
 __global__ void features_kernel(const double *x0, const double *ld, const double *lg, double t,
@@ -808,9 +870,8 @@ inline unsigned nb(int64_t n, int t = 256) { return (unsigned)((n + t - 1) / t);
 }  // namespace
 
 hipError_t mlp_gemm(const uint16_t *A, int64_t a_r, int64_t a_c, const uint16_t *B, int64_t b_r,
-                    int64_t b_c, float *C, int64_t ldc, int M, int N, int K, const float *bias,
-                    int accumulate, hipStream_t s, float *work, int64_t work_len, int epi,
-                    uint16_t *Cb, int *parts) {
+                    int64_t b_c, float *C, int64_t ldc, int M, int N, int K, hipStream_t s,
+                    float *work, int64_t work_len, int *parts) {
   if (M <= 0 || N <= 0 || K <= 0 || M % 16 || N % 16 || K % 16) return hipErrorInvalidValue;
   // (64, 64) tiles where N allows, (16, 64) for a 16-row product, else
   // (64, 16)
@@ -821,12 +882,9 @@ hipError_t mlp_gemm(const uint16_t *A, int64_t a_r, int64_t a_c, const uint16_t 
   // split K (a workspace given) until about 512 blocks (two per CU), each
   // part at least two chunks
   const int chunks = (K + GBK - 1) / GBK;
-  if (epi < EPI_NONE || epi > EPI_GELU || (epi == EPI_GELU && (!Cb || accumulate)) ||
-      (work && !parts) || (parts && (bias || accumulate || ldc != N)))
-    return hipErrorInvalidValue;
+  if ((work && !parts) || (parts && ldc != N)) return hipErrorInvalidValue;
   int S = 1;
-  while (epi == EPI_NONE && work && gm * gn * S < 512 && chunks >= 4 * S &&
-         (int64_t)2 * S * M * N <= work_len)
+  while (work && gm * gn * S < 512 && chunks >= 4 * S && (int64_t)2 * S * M * N <= work_len)
     S *= 2;
   const int cpc = (chunks + S - 1) / S;
   // 16-byte loads when every run of 8 along the unit stride is aligned
@@ -836,25 +894,17 @@ hipError_t mlp_gemm(const uint16_t *A, int64_t a_r, int64_t a_c, const uint16_t 
   };
   const bool vec = al(A, a_r, a_c) && al(B, b_c, b_r);
   const dim3 grid((unsigned)gn, (unsigned)gm, (unsigned)S);
-#define CHX_GEMM_GO(bm, bn, v, ep)                                                               \
-  hipLaunchKernelGGL((gemm_tile_kernel<bm, bn, v, ep>), grid, dim3(256), 0, s, A, a_r, a_c, B,   \
-                     b_r, b_c, C, ldc, M, N, K, cpc, bias, accumulate, work, Cb)
-#define CHX_GEMM_LAUNCH(bm, bn, ep)                                                              \
-  do {                                                                                          \
-    if (vec) CHX_GEMM_GO(bm, bn, true, ep);                                                     \
-    else CHX_GEMM_GO(bm, bn, false, ep);                                                        \
+#define CHX_GEMM_GO(bm, bn, v)                                                                 \
+  hipLaunchKernelGGL((gemm_tile_kernel<bm, bn, v>), grid, dim3(256), 0, s, A, a_r, a_c, B,     \
+                     b_r, b_c, C, ldc, M, N, K, cpc, work)
+#define CHX_GEMM_LAUNCH(bm, bn)        \
+  do {                                 \
+    if (vec) CHX_GEMM_GO(bm, bn, true); \
+    else CHX_GEMM_GO(bm, bn, false);   \
   } while (0)
-  // the activation epilogues exist for the 256-wide layers only
-  if (BN == 16) {
-    if (epi != EPI_NONE) return hipErrorInvalidValue;
-    CHX_GEMM_LAUNCH(64, 16, EPI_NONE);
-  } else if (BM == 16) {
-    if (epi == EPI_GELU) CHX_GEMM_LAUNCH(16, 64, EPI_GELU);
-    else CHX_GEMM_LAUNCH(16, 64, EPI_NONE);
-  } else {
-    if (epi == EPI_GELU) CHX_GEMM_LAUNCH(64, 64, EPI_GELU);
-    else CHX_GEMM_LAUNCH(64, 64, EPI_NONE);
-  }
+  if (BN == 16) CHX_GEMM_LAUNCH(64, 16);
+  else if (BM == 16) CHX_GEMM_LAUNCH(16, 64);
+  else CHX_GEMM_LAUNCH(64, 64);
 #undef CHX_GEMM_LAUNCH
 #undef CHX_GEMM_GO
   if (parts) *parts = S;
@@ -894,21 +944,15 @@ hipError_t gate_scatter(int64_t n2, const int64_t *orbit, const int8_t *label2, 
   hipLaunchKernelGGL(gate_scatter_kernel, dim3(nb(n2)), dim3(256), 0, s, n2, orbit, label2, label);
   return hipGetLastError();
 }
-hipError_t mlp_grad_step(const GradParts &gp, float *p, uint16_t *pb, uint16_t *pbF, float *g,
+hipError_t mlp_grad_step(const GradParts &gp, float *p, uint16_t *pbF, float *g,
                          float *m, float *v, const uint8_t *mask, int step, float lr, float b1,
                          float b2, float eps, float wd, float bc1, float bc2, hipStream_t s) {
-  hipLaunchKernelGGL(grad_step_kernel, dim3(nb(MLP_NPARAM)), dim3(256), 0, s, gp, p, pb, pbF, g, m,
+  hipLaunchKernelGGL(grad_step_kernel, dim3(nb(MLP_NPARAM)), dim3(256), 0, s, gp, p, pbF, g, m,
                      v, mask, step, lr, b1, b2, eps, wd, bc1, bc2);
   return hipGetLastError();
 }
-hipError_t mlp_weights_bf16(const float *p, uint16_t *pb, uint16_t *pbF, hipStream_t s) {
-  hipLaunchKernelGGL(weights_bf16_kernel, dim3(nb(MLP_NPARAM)), dim3(256), 0, s, p, pb, pbF);
-  return hipGetLastError();
-}
-hipError_t mlp_batch_input(const float *feat, const int64_t *rows, int B, int64_t n_valid,
-                           const float *mean, const float *istd, uint16_t *X, hipStream_t s) {
-  hipLaunchKernelGGL(batch_input_kernel, dim3(nb(B)), dim3(256), 0, s, feat, rows, B, n_valid,
-                     mean, istd, X);
+hipError_t mlp_weights_bf16(const float *p, uint16_t *pbF, hipStream_t s) {
+  hipLaunchKernelGGL(weights_bf16_kernel, dim3(nb(MLP_NPARAM)), dim3(256), 0, s, p, pbF);
   return hipGetLastError();
 }
 hipError_t mlp_init_params(float *p, uint8_t *mask, uint64_t seed, hipStream_t s) {
@@ -923,8 +967,14 @@ hipError_t mlp_feature_stats(const float *feat, int64_t n, float *mean, float *i
                      mean, istd);
   return hipGetLastError();
 }
-hipError_t mlp_infer_out(const float *Z3, int B, float *pc, float *conf, hipStream_t s) {
-  hipLaunchKernelGGL(infer_out_kernel, dim3(nb(B)), dim3(256), 0, s, Z3, B, pc, conf);
+hipError_t mlp_infer(const float *feat, int64_t n, const float *mean, const float *istd,
+                     const float *p, const uint16_t *pbF, float *pc, float *conf,
+                     hipStream_t s) {
+  if (n <= 0) return n == 0 ? hipSuccess : hipErrorInvalidValue;
+  const int64_t tiles = (n + IN_R - 1) / IN_R;
+  const int64_t grid = tiles < IN_GRID ? tiles : IN_GRID;
+  hipLaunchKernelGGL(infer_kernel, dim3((unsigned)grid), dim3(64 * TR_W), 0, s, feat, n, mean,
+                     istd, p, pbF, pc, conf);
   return hipGetLastError();
 }
 hipError_t mlp_features(const double *x0, const double *ld, const double *lg, double t, int64_t n,

@@ -120,6 +120,30 @@ def test_forward_matches_oracle(env):
     g.close()
 
 
+# one row, a row tile and its neighbours, two tiles of a block's 32 rows, and
+# more rows than one pass of the whole grid (512 blocks of 32 rows)
+@pytest.mark.parametrize("n", [1, 15, 17, 32, 33, 16383, 16385])
+def test_infer_row_counts(env, n):
+    torch, P, M, O = env
+    say(f"case: gate inference of {n} rows")
+    F = random_features(4, n)
+    mu, istd = M.zscore_stats(random_features(3, 5000).astype(np.float64))
+    p = random_params(M, 2)
+    if n > 2:
+        F[n // 2] = np.nan  # a row without a value touches no other row
+    g = P.Gate(1)
+    g.set(p, mu.astype(np.float32), istd.astype(np.float32))
+    pg, cg = g.infer(F)
+    _, mu32, is32 = g.get()
+    g.close()
+    fin = np.isfinite(F).all(1)
+    X = M.inputs(F[fin], mu32, is32, rounding=True)
+    pr = M.probabilities(M.forward(p.astype(np.float64), X, rounding=True)[4])
+    assert np.abs(pg[fin] - pr).max() <= 2e-3
+    assert np.array_equal(cg[fin], np.maximum(pg[fin], 1 - pg[fin]))
+    assert np.isnan(pg[~fin]).all() and np.isnan(cg[~fin]).all()
+
+
 # 4104 rows: a ragged batch (not a multiple of 16; the products' K is not a
 # multiple of their 32-deep chunks) split over K; 40 rows: fewer rows than
 # one 64-row tile
