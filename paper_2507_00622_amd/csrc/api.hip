@@ -411,7 +411,7 @@ chx_status advance(chx_ensemble *e, int64_t s_end) {
   return CHX_OK;
 }
 
-chx_status results(chx_ensemble *e, chx_result *res, double *gali_scratch) {
+chx_status results(chx_ensemble *e, chx_result *res) {
   if (!e) return fail(CHX_ERR_INVALID_ARG, "ensemble is NULL");
   if (!res) return fail(CHX_ERR_INVALID_ARG, "result is NULL");
   if (e->s_done == 0) return fail(CHX_ERR_INVALID_ARG, "no steps integrated yet");
@@ -472,7 +472,7 @@ chx_status results(chx_ensemble *e, chx_result *res, double *gali_scratch) {
   }
   oa.r = d;
   hipError_t he = launch_masked_fill(e->x0, e->mask, n, pl.N, oa, pl.m_s, pl.n_l, s);
-  if (he == hipSuccess) he = launch_finalize(e->args, oa, pl.N, gali_scratch, s);
+  if (he == hipSuccess) he = launch_finalize(e->args, oa, pl.N, s);
   if (!e->device) {
     for (auto &o : outs)
       if (*o.dev && he == hipSuccess) he = hipMemcpyAsync(o.host, *o.dev, o.bytes, hipMemcpyDeviceToHost, s);

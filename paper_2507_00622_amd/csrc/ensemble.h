@@ -69,9 +69,7 @@ void release(chx_ensemble *e);
 chx_status create(const chx_system *sys, const double *x0, const uint8_t *mask, int64_t n,
                   const chx_options *opt, chx_ensemble **out, Arena *arena = nullptr);
 chx_status advance(chx_ensemble *e, int64_t s_end);
-// gali_scratch: n_active * gali_kmax * 2N doubles for the GALI QR, or null
-// to allocate it
-chx_status results(chx_ensemble *e, chx_result *res, double *gali_scratch = nullptr);
+chx_status results(chx_ensemble *e, chx_result *res);
 chx_status subset(chx_ensemble *e, const uint8_t *keep, chx_ensemble **out, int64_t **orbit_out);
 // custom.hip: user systems compiled at run time
 size_t custom_rk_lds_per_lane(bool general, bool adaptive, int N, int M);

@@ -2,7 +2,7 @@
 // integration of chx_integrate_ensemble for callers that cannot allocate
 // device memory.  Every buffer the call needs beyond the caller's inputs and
 // outputs (active-orbit index, compaction counts, the ensemble's state in
-// its structure-of-arrays layout, the GALI QR copies) is carved from one
+// its structure-of-arrays layout) is carved from one
 // file-scope device array, `scratch`, of CHX_NOALLOC_MAX_BYTES.  Each GPU
 // holds its own copy of the array, at its own address, from the loading of
 // this code object until the process ends.
@@ -80,7 +80,8 @@ extern "C" chx_status chx_integrate_ensemble_noalloc(const chx_system *sys, cons
   if (n < 0) return fail(CHX_ERR_INVALID_ARG, "n must be >= 0");
   if (n == 0) return CHX_OK;
   if (!x0) return fail(CHX_ERR_INVALID_ARG, "x0 is NULL");
-  // the workspace the call needs, with every orbit active (an upper bound)
+  // the workspace the call needs, with every orbit active (an upper bound;
+  // the limit the header states counts the GALI vectors once more)
   const int D = pl.D, M = pl.M;
   if (n > (int64_t)(CHX_NOALLOC_MAX_BYTES / 8))
     return fail(CHX_ERR_INVALID_ARG, "n = %lld initial conditions need more than the %llu-byte workspace of the allocation-free entry", (long long)n, (unsigned long long)CHX_NOALLOC_MAX_BYTES);
@@ -102,16 +103,8 @@ extern "C" chx_status chx_integrate_ensemble_noalloc(const chx_system *sys, cons
   chx_ensemble *e = nullptr;
   st = create(sys, x0, mask, n, opt, &e, &ar);
   if (st) return st;
-  double *gq = nullptr;
-  if (gali) {
-    gq = ar.take<double>((size_t)e->n_active * pl.kmax * D);
-    if (e->n_active > 0 && !gq) {
-      release(e);
-      return fail(CHX_ERR_INTERNAL, "workspace estimate too small");
-    }
-  }
   st = advance(e, e->pl.n_total);
-  if (!st) st = results(e, res, gq);
+  if (!st) st = results(e, res);
   release(e);
   return st;
 }

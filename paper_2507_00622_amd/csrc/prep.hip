@@ -9,6 +9,7 @@
 
 #include "chx_internal.h"
 #include "device_math.h"
+#include "fput_row.h"
 #include "fput_sys.h"
 #include "systems.h"
 #include "systems_dp.h"
@@ -152,7 +153,7 @@ __global__ void init_kernel(StepArgs a, InitArgs ia) {
 }
 
 // ---- outputs --------------------------------------------------------------
-__global__ void finalize_kernel(StepArgs a, OutArgs o, int N, double *gscratch) {
+__global__ void finalize_kernel(StepArgs a, OutArgs o, int N) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= a.n) return;
   const int D = 2 * N;
@@ -197,38 +198,108 @@ __global__ void finalize_kernel(StepArgs a, OutArgs o, int N, double *gscratch) 
       const double g = 0.5 * (log(a.gm[k * P + i]) + (double)a.ge[k * P + i] * LN2);
       r.lyap[j * a.n_l + v] = (bad || !(te > 0.0)) ? NAN : g / te;
     }
-  if (r.gali && o.gali_kmax >= 2) {
-    const int km = o.gali_kmax;
-    double *g = r.gali + j * (km - 1);
-    if (bad) {
-      for (int k = 2; k <= km; ++k) g[k - 2] = NAN;
-      return;
+}
+
+// GALI_k = product of the diagonal of R in a modified Gram-Schmidt QR of the
+// k leading unit vectors (the volume the singular values give), k = 2..km;
+// NaN for orbits without a result.
+//
+// What bounds both forms is the vectors' traffic between the products, so
+// the copies being orthogonalised never leave the CU.  Up to 2N = 8 an orbit
+// is one lane's, its copies in LDS, component f of thread t at
+// f * blockDim + t.
+extern __shared__ double gali_lds[];
+__global__ void gali_lane_kernel(StepArgs a, OutArgs o, int N) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= a.n) return;
+  const int D = 2 * N, km = o.gali_kmax, T = blockDim.x;
+  const int64_t P = a.pitch;
+  const int st = a.st[i];
+  double *g = o.r.gali + o.idx[i] * (km - 1);
+  if (st == CHX_ORBIT_NONFINITE || st == CHX_ORBIT_STEP_FAILED) {
+    for (int k = 2; k <= km; ++k) g[k - 2] = NAN;
+    return;
+  }
+  double *u = gali_lds + threadIdx.x;
+  double prod = 1.0;
+  for (int v = 0; v < km; ++v) {
+    double *uv = u + (size_t)v * D * T;
+    double r2 = 0.0;
+    for (int c = 0; c < D; ++c) {
+      const double e = a.w[((int64_t)v * D + c) * P + i];
+      uv[c * T] = e;
+      r2 += e * e;
     }
-    // GALI_k = product of the diagonal of R in a modified Gram-Schmidt QR of
-    // the k leading unit vectors (the volume the singular values give).
-    double *u = gscratch + i * (int64_t)km * D;
-    double prod = 1.0;
-    for (int v = 0; v < km; ++v) {
-      double r2 = 0.0;
-      for (int c = 0; c < D; ++c) {
-        const double e = a.w[((int64_t)v * D + c) * P + i];
-        u[v * D + c] = e;
-        r2 += e * e;
-      }
-      const double rn = sqrt(r2);
-      for (int c = 0; c < D; ++c) u[v * D + c] /= rn;
-      for (int l = 0; l < v; ++l) {
-        double d = 0.0;
-        for (int c = 0; c < D; ++c) d += u[l * D + c] * u[v * D + c];
-        for (int c = 0; c < D; ++c) u[v * D + c] -= d * u[l * D + c];
-      }
-      double rr = 0.0;
-      for (int c = 0; c < D; ++c) rr += u[v * D + c] * u[v * D + c];
-      const double rj = sqrt(rr);
-      for (int c = 0; c < D; ++c) u[v * D + c] /= rj;
-      prod *= rj;
-      if (v >= 1) g[v - 1] = prod;
+    const double rn = sqrt(r2);
+    for (int c = 0; c < D; ++c) uv[c * T] /= rn;
+    for (int l = 0; l < v; ++l) {
+      const double *ul = u + (size_t)l * D * T;
+      double d = 0.0;
+      for (int c = 0; c < D; ++c) d += ul[c * T] * uv[c * T];
+      for (int c = 0; c < D; ++c) uv[c * T] -= d * ul[c * T];
     }
+    double rr = 0.0;
+    for (int c = 0; c < D; ++c) rr += uv[c * T] * uv[c * T];
+    const double rj = sqrt(rr);
+    for (int c = 0; c < D; ++c) uv[c * T] /= rj;
+    prod *= rj;
+    if (v >= 1) g[v - 1] = prod;
+  }
+}
+
+// Longer vectors: a 16-lane row per orbit, lane l holding components l and
+// (CPL = 2) l + 16; norms and dot products are row sums, and each lane
+// keeps its components of the earlier vectors in LDS, where only it reads
+// them (no barrier).  A block's 16 orbits share the 128-byte lines of the
+// vectors' columns.  65,536 FPU chains of 16 masses, GALI_2..16: one lane
+// per orbit with its copies in global memory took 6.7 ms of a 26.5 ms call,
+// which now takes 19.5 ms.
+template <int CPL>
+__global__ void gali_row_kernel(StepArgs a, OutArgs o, int N) {
+  using fputrow::row_sum;
+  const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 4;
+  if (i >= a.n) return;  // whole rows leave
+  const int lane = threadIdx.x & 15;
+  const int D = 2 * N, km = o.gali_kmax, T = blockDim.x;
+  const int64_t P = a.pitch;
+  const int st = a.st[i];
+  double *g = o.r.gali + o.idx[i] * (km - 1);
+  if (st == CHX_ORBIT_NONFINITE || st == CHX_ORBIT_STEP_FAILED) {
+    for (int k = 2 + lane; k <= km; k += 16) g[k - 2] = NAN;
+    return;
+  }
+  double *u = gali_lds + threadIdx.x;
+  auto norm2 = [](const double (&e)[CPL]) {
+    double t = e[0] * e[0];
+    if constexpr (CPL == 2) t = __builtin_fma(e[1], e[1], t);
+    return row_sum(t);
+  };
+  double prod = 1.0;
+  for (int v = 0; v < km; ++v) {
+    double e[CPL];
+#pragma unroll
+    for (int h = 0; h < CPL; ++h) {
+      const int c = lane + 16 * h;
+      e[h] = c < D ? a.w[((int64_t)v * D + c) * P + i] : 0.0;
+    }
+    const double rn = sqrt(norm2(e));
+#pragma unroll
+    for (int h = 0; h < CPL; ++h) e[h] /= rn;
+    for (int l = 0; l < v; ++l) {
+      double b[CPL];
+#pragma unroll
+      for (int h = 0; h < CPL; ++h) b[h] = u[(size_t)(l * CPL + h) * T];
+      double t = b[0] * e[0];
+      if constexpr (CPL == 2) t = __builtin_fma(b[1], e[1], t);
+      const double d = row_sum(t);
+#pragma unroll
+      for (int h = 0; h < CPL; ++h) e[h] = __builtin_fma(-d, b[h], e[h]);
+    }
+    const double rj = sqrt(norm2(e));
+#pragma unroll
+    for (int h = 0; h < CPL; ++h) u[(size_t)(v * CPL + h) * T] = e[h] / rj;
+    prod *= rj;
+    if (v >= 1 && lane == 0) g[v - 1] = prod;
   }
 }
 
@@ -493,28 +564,27 @@ hipError_t launch_init(const StepArgs &a, const InitArgs &ia, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_finalize(const StepArgs &a, const OutArgs &oa, int ndof, double *given,
-                           hipStream_t s) {
+hipError_t launch_finalize(const StepArgs &a, const OutArgs &oa, int ndof, hipStream_t s) {
   if (a.n == 0) return hipSuccess;
-  double *scratch = nullptr;
-  hipError_t e;
+  hipLaunchKernelGGL(finalize_kernel, dim3(blocks_for(a.n)), dim3(TPB), 0, s, a, oa, ndof);
   if (oa.r.gali && oa.gali_kmax >= 2) {
-    if (given) {
-      scratch = given;
-    } else {
-      e = hipMallocAsync((void **)&scratch,
-                         sizeof(double) * (size_t)a.n * oa.gali_kmax * 2 * ndof, s);
-      if (e != hipSuccess) return e;
-    }
+    // LDS per thread, and the largest block that keeps to 64 KB (a 64-thread
+    // block needs at most 32 KB: 8 vectors of 8 components per lane, 32
+    // vectors of two components per lane)
+    const int D = 2 * ndof;
+    const bool rows = D > 8;
+    const size_t per = sizeof(double) * oa.gali_kmax * (rows ? (D > 16 ? 2 : 1) : D);
+    int tpb = TPB;
+    while (tpb > 64 && per * tpb > 65536) tpb /= 2;
+    const dim3 grid(blocks_for(rows ? a.n * 16 : a.n, tpb));
+    if (!rows)
+      hipLaunchKernelGGL(gali_lane_kernel, grid, dim3(tpb), per * tpb, s, a, oa, ndof);
+    else if (D > 16)
+      hipLaunchKernelGGL(gali_row_kernel<2>, grid, dim3(tpb), per * tpb, s, a, oa, ndof);
+    else
+      hipLaunchKernelGGL(gali_row_kernel<1>, grid, dim3(tpb), per * tpb, s, a, oa, ndof);
   }
-  hipLaunchKernelGGL(finalize_kernel, dim3(blocks_for(a.n)), dim3(TPB), 0, s, a, oa, ndof,
-                     scratch);
-  e = hipGetLastError();
-  if (scratch && scratch != given) {
-    hipError_t e2 = hipFreeAsync(scratch, s);
-    if (e == hipSuccess) e = e2;
-  }
-  return e;
+  return hipGetLastError();
 }
 
 hipError_t launch_masked_fill(const double *x0, const uint8_t *mask, int64_t n_all, int ndof,

@@ -306,3 +306,28 @@ def test_fput_without_vectors(env, N):
     assert np.max(state_err(g["x_final"], o["x_final"])) < 1e-9
     assert np.max(np.abs(g["ld"] / o["ld"] - 1)) < 1e-9
     assert np.max(np.abs(g["energy_err"] - o["energy_err"]) / np.maximum(1.0, E)) < 1e-12
+
+
+# the GALI forms at their edges: 2N = 8 is the longest vector of the lane
+# form, 10 and 16 fit one component per lane of a row, 18 and 32 take two;
+# 4, 16 and 32 vectors; 21 orbits end inside a block of 16 rows
+@pytest.mark.parametrize("N,kmax", [(4, 4), (5, 4), (8, 16), (9, 4), (16, 32)])
+def test_gali_forms(env, N, kmax):
+    torch, P, O = env
+    n = 21
+    say(f"case: GALI_2..{kmax} of FPU N={N}, n={n}, masked and non-finite rows")
+    so, sg = O.fput(N), P.fput(N)
+    x0 = O.fput_ic(so, S.fput_mode_draws(4000 + N, n))
+    x0[7, 0] = np.nan
+    mask = np.ones(n, np.uint8)
+    mask[3] = 0
+    w0 = S.deviation_vectors(4100 + N, n, kmax, 2 * N)
+    kw = dict(dt=0.02, T=0.5, indicators=O.IND_GALI, gali_kmax=kmax)
+    g = run_gpu(env, sg, x0, mask, w0, **kw)
+    o = O.integrate(so, x0, O.Run(**kw), w0=w0, mask=mask)
+    assert np.array_equal(g["status"], o["status"])
+    assert np.isnan(g["gali"][[3, 7]]).all()
+    ok = (mask == 1) & (g["status"] == 0)
+    # both are products of R_kk of unit vectors, each with an absolute error
+    # of a few 1e-16
+    assert np.abs(g["gali"][ok] - o["gali"][ok]).max() < 1e-13
