@@ -102,6 +102,24 @@ chx_status check_system(const chx_system *sys) {
   return CHX_OK;
 }
 
+// Whether the SALI/GALI set is kept as coordinates in the frame of the
+// Lyapunov set (StepArgs::frame) instead of being integrated.  It needs the
+// full set (n_l = 2N, orthonormal after every checkpoint) and the fixed
+// step (the adaptive solver's error estimate takes in every vector).
+// The coordinates lose what the frame loses: its vectors come out of the
+// Gram-Schmidt orthonormal to 1e-16 times the stretching ratio of one
+// checkpoint interval.  With the step resolving the motion (rate times step
+// below about 0.3) K = 16 steps keep that below 1e-12; longer intervals
+// integrate the set.
+int frame_of(const chx_system *sys, const Plan &p) {
+  const int N = p.N;
+  if (p.m_s < 2 || p.n_l != 2 * N || p.K > 16) return 0;
+  if (sys->kind == CHX_SYS_FPUT) return 0;
+  if (p.o.integrator == CHX_INT_DOP853_ADAPTIVE) return 0;
+  // the lane kernels: the SALI pair, the square-root LD
+  return p.m_s == 2 && !((p.o.indicators & CHX_IND_LD) && p.o.ld_p != 0.5);
+}
+
 chx_status make_plan(const chx_system *sys, const chx_options *opt, Plan *p) {
   if (!opt) return fail(CHX_ERR_INVALID_ARG, "options is NULL");
   chx_options o = *opt;
@@ -167,6 +185,7 @@ chx_status make_plan(const chx_system *sys, const chx_options *opt, Plan *p) {
   p->K = o.renorm_every;
   p->kmax = kmax;
   p->n_total = (int64_t)nr;
+  p->frame = frame_of(sys, *p);
   const int sk = sys->kind;
   const bool fput_rk = o.integrator != CHX_INT_YOSHIDA4 && sk == CHX_SYS_FPUT;
   if (fput_rk && p->M > 4) {
@@ -328,6 +347,7 @@ chx_status create(const chx_system *sys, const double *x0, const uint8_t *mask, 
   a.K = pl.K;
   a.m_s = pl.m_s;
   a.n_l = pl.n_l;
+  a.frame = pl.frame;
   a.ind = pl.o.indicators;
   a.early_exit = pl.o.early_exit ? 1 : 0;
   a.dt = pl.o.dt;

@@ -5,8 +5,10 @@
 // 512-byte segments):
 //   x   [2N][pitch]            phase-space state
 //   w   [M][2N][pitch]         deviation vectors: the SALI/GALI set
-//                              (m_s vectors) followed by the Lyapunov set
-//                              (n_l vectors), M = m_s + n_l
+//                              (m_s vectors, or their coordinates in the
+//                              frame of the Lyapunov set, StepArgs::frame)
+//                              followed by the Lyapunov set (n_l vectors),
+//                              M = m_s + n_l
 //   gm  [M][pitch], ge [M][pitch]  growth product of squared norms kept as
 //                              mantissa (double) and binary exponent (int):
 //                              ln-growth = (ln gm + ge ln 2) / 2
@@ -56,6 +58,8 @@ struct StepArgs {
   int K;            // checkpoint period
   int m_s;          // SALI/GALI vectors (the first m_s of w)
   int n_l;          // Lyapunov vectors (the next n_l)
+  int frame;        // 1: w's SALI/GALI rows hold the set's coordinates in the
+                    // frame of the full Lyapunov set (frame_of in api.hip)
   uint32_t ind;     // CHX_IND_* bits
   int early_exit;
   double dt;

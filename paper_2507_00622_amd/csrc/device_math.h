@@ -21,6 +21,13 @@ __device__ __forceinline__ double rsqrt_nr(double a) {
   return __builtin_fma(0.5 * y, e, y);
 }
 
+// 1 / y for y = rsqrt_nr(a), to rounding: a y is within 1e-14 of it, and one
+// Newton step of the reciprocal removes y's own error.
+__device__ __forceinline__ double rsqrt_inverse(double a, double y) {
+  const double s = a * y;
+  return __builtin_fma(s, __builtin_fma(-s, y, 1.0), s);
+}
+
 // sqrt(|a|) for the Lagrangian-descriptor integrand, relative error below
 // 1e-14: one Goldschmidt step from the hardware reciprocal-root estimate
 // (error 1.5 e^2 for an estimate with relative error e; e <= 5.3e-8 was

@@ -12,6 +12,7 @@ namespace host {
 struct Plan {
   chx_options o;
   int N, D, m_s, n_l, M, K, kmax;
+  int frame;  // the SALI/GALI set is kept in the frame of the Lyapunov set
   int64_t n_total;
 };
 

@@ -46,9 +46,23 @@ struct has_hamiltonian<S, std::void_t<decltype(&S::hamiltonian)>> : std::true_ty
 // it; MS = -1 reads it from the launch arguments.
 // CO: coherent loads and stores of the orbit's state (gld/gst), for the
 // persistent kernel.
-template <class S, int M, bool GP, int MS = -1, bool CO = false>
+// FR: the SALI/GALI set in the frame of the Lyapunov set.  The tangent map
+// is linear and the 2N Lyapunov vectors, orthonormal after every checkpoint,
+// span the tangent space: a vector that is Q c at one checkpoint is
+// (Phi Q) c = Q' (R c) at the next, with Q' R = Phi Q the Gram-Schmidt that
+// the checkpoint computes anyway.  So w[0..MS-1] hold the coordinates c, no
+// kick or drift touches them, and a checkpoint multiplies them by the upper
+// triangular R; norms, SALI and GALI are those of c, Q' being orthonormal.
+// Q = I at t = 0, so the set starts as the caller's vectors.  Henon-Heiles
+// with SALI and four exponents integrates 4 vectors instead of 6, with the
+// FP64 ALU as the bound either way: a 992,552-orbit section, 3000 steps,
+// 22.0 -> 19.0 ms with Yoshida-4; 212,700 orbits, 1000 steps of DOP853 31.2 ->
+// 23.7 ms (5 passes a step instead of 7).
+template <class S, int M, bool GP, int MS = -1, bool CO = false, bool FR = false>
 struct LaneOrbit {
   static constexpr int N = S::N, D = 2 * N, MM = (M > 0 ? M : 1);
+  static_assert(!FR || (MS > 0 && M == MS + D), "a frame is the full Lyapunov set");
+  static constexpr int V0 = FR ? MS : 0;  // first vector that is integrated
   static constexpr int UNROLL = (N == 2 && M >= 4) ? 2 : 1;
   double x[D], w[MM][D], gm[MM];
   int ge[MM];
@@ -104,7 +118,7 @@ struct LaneOrbit {
     double Hs[S::NH];
     S::hess_scaled(x, hk, Hs, a.prm);
 #pragma unroll
-    for (int v = 0; v < M; ++v) {
+    for (int v = V0; v < M; ++v) {
       double dq[N];
 #pragma unroll
       for (int r = 0; r < N; ++r) dq[r] = w[v][r];
@@ -129,7 +143,7 @@ struct LaneOrbit {
 #pragma unroll
     for (int r = 0; r < N; ++r) x[r] = __builtin_fma(c, x[N + r], x[r]);
 #pragma unroll
-    for (int v = 0; v < M; ++v)
+    for (int v = V0; v < M; ++v)
 #pragma unroll
       for (int r = 0; r < N; ++r) w[v][r] = __builtin_fma(c, w[v][N + r], w[v][r]);
   }
@@ -179,6 +193,74 @@ struct LaneOrbit {
     kick_vectors(a, k.hk0);
   }
 
+  // SALI/GALI set: each vector back to unit length
+  __device__ __forceinline__ void unit_set(int m_s) {
+#pragma unroll
+    for (int v = 0; v < M; ++v) {
+      if (v < m_s) {
+        double r2 = 0.0;
+#pragma unroll
+        for (int c = 0; c < D; ++c) r2 = __builtin_fma(w[v][c], w[v][c], r2);
+        const double inv = rsqrt_nr(r2);
+#pragma unroll
+        for (int c = 0; c < D; ++c) w[v][c] *= inv;
+        grow(gm[v], ge[v], r2);
+      }
+    }
+  }
+  // SALI^2 of the first two vectors, with its minimum and first crossing
+  __device__ __forceinline__ double sali(const StepArgs &a, double t) {
+    double sp = 0.0, sm = 0.0;
+#pragma unroll
+    for (int c = 0; c < D; ++c) {
+      const double ap = w[0][c] + w[MM > 1 ? 1 : 0][c];
+      const double am = w[0][c] - w[MM > 1 ? 1 : 0][c];
+      sp = __builtin_fma(ap, ap, sp);
+      sm = __builtin_fma(am, am, sm);
+    }
+    const double s2 = __builtin_fmin(sp, sm);
+    slast2 = s2;
+    smin2 = __builtin_fmin(smin2, s2);
+    if (s2 < a.thr2 && __builtin_isnan(tch)) tch = t;
+    return s2;
+  }
+  // Lyapunov set: modified Gram-Schmidt in vector order; FR: with it
+  // c <- R c of the set's coordinates, column by column of R
+  __device__ __forceinline__ void gram_schmidt(int m_s) {
+#pragma unroll
+    for (int q = 0; q < M; ++q) {
+      if (q >= m_s) {
+#pragma unroll
+        for (int l = 0; l < q; ++l) {
+          if (l >= m_s) {
+            double d = 0.0;
+#pragma unroll
+            for (int c = 0; c < D; ++c) d = __builtin_fma(w[l][c], w[q][c], d);
+#pragma unroll
+            for (int c = 0; c < D; ++c) w[q][c] = __builtin_fma(-d, w[l][c], w[q][c]);
+            if constexpr (FR) {
+#pragma unroll
+              for (int v = 0; v < MS; ++v)
+                w[v][l - MS] = __builtin_fma(d, w[v][q - MS], w[v][l - MS]);
+            }
+          }
+        }
+        double r2 = 0.0;
+#pragma unroll
+        for (int c = 0; c < D; ++c) r2 = __builtin_fma(w[q][c], w[q][c], r2);
+        const double inv = rsqrt_nr(r2);
+#pragma unroll
+        for (int c = 0; c < D; ++c) w[q][c] *= inv;
+        grow(gm[q], ge[q], r2);
+        if constexpr (FR) {
+          const double rq = rsqrt_inverse(r2, inv);
+#pragma unroll
+          for (int v = 0; v < MS; ++v) w[v][q - MS] *= rq;
+        }
+      }
+    }
+  }
+
   // Checkpoint at time t; returns false when the orbit stops (status set).
   __device__ bool checkpoint(const StepArgs &a, double t) {
     const int m_s = MS >= 0 ? MS : a.m_s;
@@ -198,56 +280,15 @@ struct LaneOrbit {
       for (int r = 0; r < N; ++r) r2 = __builtin_fma(x[r], x[r], r2);
       escaped = r2 > a.escape_r2;
     }
-    // SALI/GALI set: each vector back to unit length
-#pragma unroll
-    for (int v = 0; v < M; ++v) {
-      if (v < m_s) {
-        double r2 = 0.0;
-#pragma unroll
-        for (int c = 0; c < D; ++c) r2 = __builtin_fma(w[v][c], w[v][c], r2);
-        const double inv = rsqrt_nr(r2);
-#pragma unroll
-        for (int c = 0; c < D; ++c) w[v][c] *= inv;
-        grow(gm[v], ge[v], r2);
-      }
-    }
     double s2 = 0.0;
-    if (do_sali) {
-      double sp = 0.0, sm = 0.0;
-#pragma unroll
-      for (int c = 0; c < D; ++c) {
-        const double ap = w[0][c] + w[MM > 1 ? 1 : 0][c];
-        const double am = w[0][c] - w[MM > 1 ? 1 : 0][c];
-        sp = __builtin_fma(ap, ap, sp);
-        sm = __builtin_fma(am, am, sm);
-      }
-      s2 = __builtin_fmin(sp, sm);
-      slast2 = s2;
-      smin2 = __builtin_fmin(smin2, s2);
-      if (s2 < a.thr2 && __builtin_isnan(tch)) tch = t;
-    }
-    // Lyapunov set: modified Gram-Schmidt in vector order
-#pragma unroll
-    for (int q = 0; q < M; ++q) {
-      if (q >= m_s) {
-#pragma unroll
-        for (int l = 0; l < q; ++l) {
-          if (l >= m_s) {
-            double d = 0.0;
-#pragma unroll
-            for (int c = 0; c < D; ++c) d = __builtin_fma(w[l][c], w[q][c], d);
-#pragma unroll
-            for (int c = 0; c < D; ++c) w[q][c] = __builtin_fma(-d, w[l][c], w[q][c]);
-          }
-        }
-        double r2 = 0.0;
-#pragma unroll
-        for (int c = 0; c < D; ++c) r2 = __builtin_fma(w[q][c], w[q][c], r2);
-        const double inv = rsqrt_nr(r2);
-#pragma unroll
-        for (int c = 0; c < D; ++c) w[q][c] *= inv;
-        grow(gm[q], ge[q], r2);
-      }
+    if constexpr (FR) {  // the set's coordinates follow from the Gram-Schmidt
+      gram_schmidt(m_s);
+      unit_set(m_s);
+      if (do_sali) s2 = sali(a, t);
+    } else {
+      unit_set(m_s);
+      if (do_sali) s2 = sali(a, t);
+      gram_schmidt(m_s);
     }
     if (a.ind & CHX_IND_ENERGY) {
       double e;
@@ -273,12 +314,12 @@ struct LaneOrbit {
   }
 };
 
-template <class S, int M, bool GP, int MS>
+template <class S, int M, bool GP, int MS, bool FR = false>
 __global__ void __launch_bounds__(256) lane_kernel(const StepArgs a) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= a.n) return;
   if (a.st[i] != CHX_ORBIT_OK) return;
-  LaneOrbit<S, M, GP, MS> o;
+  LaneOrbit<S, M, GP, MS, false, FR> o;
   o.load(a, i);
   const StepCoef k(a.dt);
   int64_t s = a.s_begin;
@@ -306,6 +347,13 @@ struct LaneDispatch {
     if (m == M) {
       const bool gp = (a.ind & CHX_IND_LD) && a.ld_p != 0.5;
       const int64_t grid = (a.n + block - 1) / block;
+      if constexpr (M == 2 + 2 * S::N) {
+        if (a.frame) {
+          hipLaunchKernelGGL((lane_kernel<S, M, false, 2, true>), dim3((unsigned)grid),
+                             dim3(block), 0, s, a);
+          return hipGetLastError();
+        }
+      }
       if (gp)
         hipLaunchKernelGGL((lane_kernel<S, M, true, -1>), dim3((unsigned)grid), dim3(block), 0, s,
                            a);

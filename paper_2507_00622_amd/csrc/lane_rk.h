@@ -47,9 +47,11 @@ constexpr int rec_width() {
     return S::N;
 }
 
-template <class S, int M, bool GP>
-struct RKOrbit : LaneOrbit<S, M, GP, -1> {
-  using Base = LaneOrbit<S, M, GP, -1>;
+// FR: the SALI pair in the frame of the full Lyapunov set (LaneOrbit): the
+// vector passes are those of the Lyapunov set alone.
+template <class S, int M, bool GP, bool FR = false>
+struct RKOrbit : LaneOrbit<S, M, GP, (FR ? 2 : -1), false, FR> {
+  using Base = LaneOrbit<S, M, GP, (FR ? 2 : -1), false, FR>;
   using Base::N;
   using Base::D;
   using Base::x;
@@ -227,7 +229,7 @@ struct RKOrbit : LaneOrbit<S, M, GP, -1> {
     }
     __builtin_amdgcn_sched_barrier(0);
     // (a compile-time loop: the vectors must stay in registers)
-    dop853::static_for<0, M>([&](auto vc) {
+    dop853::static_for<Base::V0, M>([&](auto vc) {
       constexpr int v = decltype(vc)::value;
       double k[12][D];  // h f(dY_i) of vector v
       dop853::static_for<0, 12>([&](auto ic) {
@@ -316,12 +318,12 @@ struct RKOrbit : LaneOrbit<S, M, GP, -1> {
 // per thread.
 extern __shared__ double lane_rk_lds[];
 
-template <class S, int M, bool GP>
+template <class S, int M, bool GP, bool FR = false>
 __global__ void __launch_bounds__(256) lane_rk_kernel(const StepArgs a) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= a.n) return;
   if (a.st[i] != CHX_ORBIT_OK) return;
-  RKOrbit<S, M, GP> o;
+  RKOrbit<S, M, GP, FR> o;
   o.load(a, i);
   const bool do_ld = (a.ind & CHX_IND_LD) != 0;
   const double h = a.dt;
@@ -476,6 +478,13 @@ struct LaneRKDispatch {
           hipLaunchKernelGGL((lane_rka_kernel<S, M, false>), dim3((unsigned)grid), dim3(block),
                              lds, s, a);
       } else {
+        if constexpr (M == 2 + 2 * S::N) {
+          if (a.frame) {
+            hipLaunchKernelGGL((lane_rk_kernel<S, M, false, true>), dim3((unsigned)grid),
+                               dim3(block), lds, s, a);
+            return hipGetLastError();
+          }
+        }
         if (gp)
           hipLaunchKernelGGL((lane_rk_kernel<S, M, true>), dim3((unsigned)grid), dim3(block),
                              lds, s, a);
