@@ -114,7 +114,12 @@ chx_status check_system(const chx_system *sys) {
 int frame_of(const chx_system *sys, const Plan &p) {
   const int N = p.N;
   if (p.m_s < 2 || p.n_l != 2 * N || p.K > 16) return 0;
-  if (sys->kind == CHX_SYS_FPUT) return 0;
+  // FPU chains: the row-pair kernel of N = 8.  (N = 16 was tried: the product
+  // with R costs 528 of the 1,920 FMAs it saves per checkpoint, and with the
+  // coordinates in LDS the pivots' chain grows by more than that: 20.3 against
+  // 19.5 to 20.4 ms for 65,536 chains and 500 steps.)
+  if (sys->kind == CHX_SYS_FPUT)
+    return p.o.integrator == CHX_INT_YOSHIDA4 && N == 8 && p.m_s <= N;
   if (p.o.integrator == CHX_INT_DOP853_ADAPTIVE) return 0;
   // the lane kernels: the SALI pair, the square-root LD
   return p.m_s == 2 && !((p.o.indicators & CHX_IND_LD) && p.o.ld_p != 0.5);

@@ -39,7 +39,10 @@ hipError_t launch_n(int M, const StepArgs &a, hipStream_t s) {
   if constexpr (N == 8) {
     if (M > 16 && M <= 24 && a.m_s <= 8) {
       const unsigned grid = (unsigned)((a.n + 7) / 8);
-      hipLaunchKernelGGL((fput_rowpair_kernel<8>), dim3(grid), dim3(64), 0, s, a);
+      if (a.frame)
+        hipLaunchKernelGGL((fput_rowpair_kernel<8, true>), dim3(grid), dim3(64), 0, s, a);
+      else
+        hipLaunchKernelGGL((fput_rowpair_kernel<8, false>), dim3(grid), dim3(64), 0, s, a);
       return hipGetLastError();
     }
   }

@@ -37,6 +37,20 @@ namespace chx {
 
 namespace fputpair {
 
+// acc += coef(lane I of the row) * x in the lanes of half H of each row only,
+// in program order
+template <int I, int H>
+__device__ __forceinline__ void fmac_bcast_half(double &acc, double coef, double x) {
+  if constexpr (H == 0)
+    asm volatile("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0x3"
+        : "+v"(acc)
+        : "v"(coef), "v"(x), "n"(I));
+  else
+    asm volatile("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xc"
+        : "+v"(acc)
+        : "v"(coef), "v"(x), "n"(I));
+}
+
 // sum over the 8 lanes of a group, identical in all of them
 __device__ __forceinline__ double grp_sum(double s) {
   using fputrow::dpp;
@@ -48,9 +62,18 @@ __device__ __forceinline__ double grp_sum(double s) {
 
 }  // namespace fputpair
 
-template <int N>
-__global__ void __launch_bounds__(64, 2) fput_rowpair_kernel(const StepArgs a) {
+// FR: slot 2 holds the SALI/GALI set's coordinates in the frame of the full
+// Lyapunov set (n_l = 2N; lane_kernel.h).  Pivot j of the Gram-Schmidt makes
+// coordinate j of every lane's vector, R_jj c_j + sum_{k>j} R_jk c_k, R_jk
+// coming from lane k of the own orbit's slot through the FMA's row_newbcast
+// operand: 272 half-row FMAs per checkpoint against 960 and the coefficients'
+// LDS round trips for integrating the slot over 10 steps.  Touched at
+// checkpoints only, the slot lives in LDS, and a third wavefront shares the
+// SIMD.  40,001 chains, 1,000 steps: 6.79 -> 6.37 ms.
+template <int N, bool FR>
+__global__ void __launch_bounds__(64, FR ? 3 : 2) fput_rowpair_kernel(const StepArgs a) {
   using namespace fputpair;
+  constexpr int VI = FR ? 2 : 3;  // slots that are integrated
   using fputrow::bcast;
   using fputrow::dpp;
   using fputrow::norm2_4;
@@ -61,7 +84,9 @@ __global__ void __launch_bounds__(64, 2) fput_rowpair_kernel(const StepArgs a) {
   constexpr int D = 2 * N;
   constexpr int G = N;         // lanes per orbit
   constexpr int OPW = 64 / G;  // orbits per wavefront
-  __shared__ __align__(16) double cf[OPW][N][2];  // slot-2 kick coefficients per orbit
+  __shared__ __align__(16) double cf[FR ? 1 : OPW][N][2];  // slot-2 kick coefficients per orbit
+  __shared__ double cset[FR ? D : 1][64];  // FR: the set's coordinates, per lane
+  double *cs = &cset[0][threadIdx.x];
   const int l = threadIdx.x & 15, row = threadIdx.x >> 4;
   const int h = l / G, c = l % G, g = threadIdx.x / G;  // g: the lane's own orbit in the wavefront
   const int64_t oA = (int64_t)blockIdx.x * OPW + 2 * row, oB = oA + 1;
@@ -84,14 +109,20 @@ __global__ void __launch_bounds__(64, 2) fput_rowpair_kernel(const StepArgs a) {
 
   double q = a.x[c * P + ooOwn];
   double p = a.x[(N + c) * P + ooOwn];
-  double w[3][D], gm[3];
+  double w[VI][D], gm[3];
   int ge[3];
 #pragma unroll
   for (int s = 0; s < 3; ++s) {
     const int vk = vk_of(s);
     const int64_t k = vk < 0 ? 0 : vk, ob = oo_of(s);
 #pragma unroll
-    for (int i = 0; i < D; ++i) w[s][i] = vk < 0 ? 0.0 : a.w[(k * D + i) * P + ob];
+    for (int i = 0; i < D; ++i) {
+      const double e = vk < 0 ? 0.0 : a.w[(k * D + i) * P + ob];
+      if (FR && s == VI)
+        cs[i * 64] = e;
+      else
+        w[s < VI ? s : 0][i] = e;
+    }
     gm[s] = vk < 0 ? 1.0 : a.gm[k * P + ob];
     ge[s] = vk < 0 ? 0 : a.ge[k * P + ob];
   }
@@ -147,15 +178,17 @@ __global__ void __launch_bounds__(64, 2) fput_rowpair_kernel(const StepArgs a) {
   auto drift = [&](double cc) {
     q = __builtin_fma(cc, p, q);
 #pragma unroll
-    for (int s = 0; s < 3; ++s)
+    for (int s = 0; s < VI; ++s)
 #pragma unroll
       for (int i = 0; i < N; ++i) w[s][i] = __builtin_fma(cc, w[s][N + i], w[s][i]);
   };
   // dp_i -= h [(kappa_i + kappa_{i+1}) dq_i - kappa_i dq_{i-1} - kappa_{i+1} dq_{i+1}]
   auto kick_vectors = [&](double hh) {
     double nhd = -(hh * (kl + kr)), hl = hh * kl;
-    cf[g][c][0] = nhd;
-    cf[g][c][1] = hl;
+    if constexpr (!FR) {
+      cf[g][c][0] = nhd;
+      cf[g][c][1] = hl;
+    }
     // two wait states between the VALU writes of nhd, hl and their DPP reads
     asm volatile("s_nop 1" : "+v"(nhd), "+v"(hl));
     // slots 0 and 1: orbit A's coefficients from lanes i, B's from 8 + i
@@ -175,22 +208,24 @@ __global__ void __launch_bounds__(64, 2) fput_rowpair_kernel(const StepArgs a) {
       w[0][N + i] = a0;
       w[1][N + i] = a1;
     });
-    // slot 2: each half its own orbit's coefficients, through LDS
-    wave_sync();
-    double cn[N], cl[N];
+    if constexpr (!FR) {
+      // slot 2: each half its own orbit's coefficients, through LDS
+      wave_sync();
+      double cn[N], cl[N];
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-      const double2 v = *(const double2 *)&cf[g][i][0];
-      cn[i] = v.x;
-      cl[i] = v.y;
-    }
-    wave_sync();  // every read above before the next kick's stores
+      for (int i = 0; i < N; ++i) {
+        const double2 v = *(const double2 *)&cf[g][i][0];
+        cn[i] = v.x;
+        cl[i] = v.y;
+      }
+      wave_sync();  // every read above before the next kick's stores
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-      double acc = __builtin_fma(cn[i], w[2][i], w[2][N + i]);
-      if (i > 0) acc = __builtin_fma(cl[i], w[2][i - 1], acc);
-      if (i + 1 < N) acc = __builtin_fma(cl[i + 1], w[2][i + 1], acc);
-      w[2][N + i] = acc;
+      for (int i = 0; i < N; ++i) {
+        double acc = __builtin_fma(cn[i], w[VI - 1][i], w[VI - 1][N + i]);
+        if (i > 0) acc = __builtin_fma(cl[i], w[VI - 1][i - 1], acc);
+        if (i + 1 < N) acc = __builtin_fma(cl[i + 1], w[VI - 1][i + 1], acc);
+        w[VI - 1][N + i] = acc;
+      }
     }
   };
   auto step_body = [&]() {
@@ -230,7 +265,11 @@ __global__ void __launch_bounds__(64, 2) fput_rowpair_kernel(const StepArgs a) {
       if (st_s && vk >= 0) {
         const int64_t k = vk, ob = s == 0 ? obA : (s == 1 ? obB : obOwn);
 #pragma unroll
-        for (int i = 0; i < D; ++i) a.w[(k * D + i) * P + ob] = w[s][i];
+        for (int i = 0; i < D; ++i) {
+          double e = w[s < VI ? s : 0][i];
+          if (FR && s == VI) e = cs[i * 64];
+          a.w[(k * D + i) * P + ob] = e;
+        }
         a.gm[k * P + ob] = gm[s];
         a.ge[k * P + ob] = ge[s];
       }
@@ -272,6 +311,15 @@ __global__ void __launch_bounds__(64, 2) fput_rowpair_kernel(const StepArgs a) {
     static_for<0, 2 * N>([&](auto jc) {
       constexpr int j = decltype(jc)::value;
       if (j < nlg) {
+        // FR: the set's coordinates j.. in flight under the dot products
+        // (read again at every pivot, not carried in registers)
+        [[maybe_unused]] double ec[D];
+        if constexpr (FR) {
+          asm volatile("" ::: "memory");
+#pragma unroll
+          for (int k = j; k < D; ++k) ec[k] = cs[k * 64];
+          asm volatile("" ::: "memory");
+        }
         double t0, t1;
         if constexpr (j < 2 * N - 1) {
           asm volatile("s_nop 1" : "+v"(w[0][0]), "+v"(w[1][0]));
@@ -291,6 +339,23 @@ __global__ void __launch_bounds__(64, 2) fput_rowpair_kernel(const StepArgs a) {
         const double r0 = bcast<j>(t0), r1 = bcast<j>(t1);
         own2[0] = l == j ? r0 : own2[0];
         own2[1] = l == j ? r1 : own2[1];
+        if constexpr (j < 2 * N - 1 || FR) {
+          const double i0 = rsqrt_nr(r0), i1 = rsqrt_nr(r1);
+          if constexpr (FR) {
+            // coordinate j of the set: row j of A's R in lanes 0..7, of
+            // B's in lanes 8..15
+            double rA = t0 * i0, rB = t1 * i1;
+            asm volatile("s_nop 1" : "+v"(rA), "+v"(rB));
+            const double rj = rsqrt_inverse(h ? r1 : r0, h ? i1 : i0);
+            double ps[4] = {rj * ec[j], 0.0, 0.0, 0.0};
+            static_for<j + 1, D>([&](auto kc) {
+              constexpr int k = decltype(kc)::value;
+              fmac_bcast_half<k, 0>(ps[k & 3], rA, ec[k]);
+              fmac_bcast_half<k, 1>(ps[k & 3], rB, ec[k]);
+            });
+            cs[j * 64] = (ps[0] + ps[1]) + (ps[2] + ps[3]);
+          }
+        }
         if constexpr (j < 2 * N - 1) {
           const double i0 = rsqrt_nr(r0), i1 = rsqrt_nr(r1);
           double n0 = -(i0 * i0), n1 = -(i1 * i1);
@@ -358,33 +423,48 @@ __global__ void __launch_bounds__(64, 2) fput_rowpair_kernel(const StepArgs a) {
     }
     bool escaped = false;
     if (a.escape_r2 > 0.0) escaped = grp_sum(q * q) > a.escape_r2;
-    // SALI/GALI set (slot 2): back to unit length (lane-local)
-    if (c < m_s) {
-      const double r2 = norm2_4<D>(w[2]);
-      const double inv = rsqrt_nr(r2);
-#pragma unroll
-      for (int i = 0; i < D; ++i) w[2][i] *= inv;
-      grow(gm[2], ge[2], r2);
-    }
     double s2 = 0.0;
-    if (do_sali) {
-      // the pair at lanes 0 and 1 of each group's slot 2: lane 0 takes
-      // lane 1's vector through quad_perm [1,1,1,1]
-      double sp[2] = {0.0, 0.0}, sm[2] = {0.0, 0.0};
+    auto set_indicators = [&]() __attribute__((always_inline)) {
+      double u[D];
 #pragma unroll
       for (int i = 0; i < D; ++i) {
-        const double other = dpp<0x55>(w[2][i]);
-        const double ap = w[2][i] + other, am = w[2][i] - other;
-        sp[i & 1] = __builtin_fma(ap, ap, sp[i & 1]);
-        sm[i & 1] = __builtin_fma(am, am, sm[i & 1]);
+        if (FR) u[i] = cs[i * 64];
+        else u[i] = w[VI - 1][i];
       }
-      s2 = __builtin_fmin(sp[0] + sp[1], sm[0] + sm[1]);
-      s2 = grp_sum(c == 0 ? s2 : 0.0);  // lane 0's value in every lane
-      slast2 = s2;
-      smin2 = __builtin_fmin(smin2, s2);
-      if (s2 < a.thr2 && __builtin_isnan(tch)) tch = t;
-    }
+      // SALI/GALI set (slot 2): back to unit length (lane-local)
+      if (c < m_s) {
+        const double r2 = norm2_4<D>(u);
+        const double inv = rsqrt_nr(r2);
+#pragma unroll
+        for (int i = 0; i < D; ++i) u[i] *= inv;
+        grow(gm[2], ge[2], r2);
+#pragma unroll
+        for (int i = 0; i < D; ++i) {
+          if (FR) cs[i * 64] = u[i];
+          else w[VI - 1][i] = u[i];
+        }
+      }
+      if (do_sali) {
+        // the pair at lanes 0 and 1 of each group's slot 2: lane 0 takes
+        // lane 1's vector through quad_perm [1,1,1,1]
+        double sp[2] = {0.0, 0.0}, sm[2] = {0.0, 0.0};
+#pragma unroll
+        for (int i = 0; i < D; ++i) {
+          const double other = dpp<0x55>(u[i]);
+          const double ap = u[i] + other, am = u[i] - other;
+          sp[i & 1] = __builtin_fma(ap, ap, sp[i & 1]);
+          sm[i & 1] = __builtin_fma(am, am, sm[i & 1]);
+        }
+        s2 = __builtin_fmin(sp[0] + sp[1], sm[0] + sm[1]);
+        s2 = grp_sum(c == 0 ? s2 : 0.0);  // lane 0's value in every lane
+        slast2 = s2;
+        smin2 = __builtin_fmin(smin2, s2);
+        if (s2 < a.thr2 && __builtin_isnan(tch)) tch = t;
+      }
+    };
+    if constexpr (!FR) set_indicators();
     gram_schmidt();
+    if constexpr (FR) set_indicators();
     if (do_energy) {
       const double dl = q - left(q), dr = right(q) - q;
       auto spring = [&](double d) {

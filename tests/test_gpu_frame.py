@@ -48,7 +48,7 @@ LANE = [("hh", 2), ("quartic", 1), ("quartic", 3), ("harmonic", 2)]
 @pytest.mark.parametrize("name,N,integ,K", [
     *[(s, N, i, k) for s, N in LANE for i, k in (("yoshida4", 10), ("dop853", 10))],
     ("hh", 2, "yoshida4", 1), ("hh", 2, "yoshida4", 16), ("hh", 2, "dop853", 16),
-    ("dp", 2, "dop853", 10)])
+    ("dp", 2, "dop853", 10), ("fput", 8, "yoshida4", 10), ("fput", 8, "yoshida4", 16)])
 def test_frame_against_integrated_set(env, name, N, integ, K):
     torch, P, O = env
     print(f"case: frame {name} N={N} {integ} K={K}", flush=True)
