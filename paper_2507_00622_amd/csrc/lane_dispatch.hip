@@ -25,6 +25,8 @@ hipError_t launch_lane_rk_harmonic2(int M, bool adaptive, const StepArgs &a, int
 hipError_t launch_lane_rk_harmonic3(int M, bool adaptive, const StepArgs &a, int block,
                             hipStream_t s);
 hipError_t launch_lane_rk_dp(int M, bool adaptive, const StepArgs &a, int block, hipStream_t s);
+bool lane_quad_wanted(int sys, const StepArgs &a);
+hipError_t launch_lane_quad(int sys, int ndof, bool adaptive, const StepArgs &a, hipStream_t s);
 
 bool lane_supported(int sys, int ndof, int M) {
   if (M < 0 || M > 4 * ndof) return false;
@@ -65,6 +67,7 @@ hipError_t launch_lane_rk(int sys, int ndof, int M, bool adaptive, const StepArg
                           int block, hipStream_t s) {
   if (!lane_supported(sys, ndof, M)) return hipErrorInvalidValue;
   if (a.n == 0) return hipSuccess;
+  if (lane_quad_wanted(sys, a)) return launch_lane_quad(sys, ndof, adaptive, a, s);
   switch (sys) {
   case SYS_HH: return launch_lane_rk_hh(M, adaptive, a, block, s);
   case SYS_QUARTIC:

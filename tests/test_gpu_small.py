@@ -1,0 +1,76 @@
+"""Small ensembles against large ones, bit for bit.
+
+Small ensembles of a SALI pair (lane systems, DOP853) or of two to four
+SALI/GALI vectors (FPU chains) run on several lanes or rows per orbit; the
+same orbits inside an ensemble beyond the kernels' size limit run on one.
+Both take the same operations in the same order, so every output agrees in
+every bit: regular and chaotic orbits, masked, non-finite, escaping and
+early-exiting ones, checkpoint periods that do not divide the run.
+"""
+import numpy as np
+import pytest
+
+import seeded_inputs as S
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    assert torch.cuda.is_available()
+    import paper_2507_00622_amd as P
+    from oracle import oracle as O
+    return torch, P, O
+
+
+def compare(env, sys_, x0, n_big, m, **kw):
+    """The first len(x0) orbits of an ensemble of n_big (x0 repeated)."""
+    torch, P, O = env
+    n, D = x0.shape
+    w0 = S.deviation_vectors(31, n, m, D)
+    mask = np.ones(n, np.uint8)
+    mask[n // 3] = 0
+    x0 = x0.copy()
+    x0[n // 2, 0] = np.nan
+    rep = -(-n_big // n)
+    t = lambda a: torch.as_tensor(a, device="cuda:0")
+    small = P.integrate_ensemble(sys_, t(x0), mask=t(mask), w0=t(w0), **kw)
+    big = P.integrate_ensemble(sys_, t(np.tile(x0, (rep, 1))), mask=t(np.tile(mask, rep)),
+                               w0=t(np.tile(w0, (rep, 1, 1))), **kw)
+    torch.cuda.synchronize()
+    assert small["status"][n // 2].item() == O.ST_NONFINITE
+    for k in small:
+        assert np.array_equal(small[k].cpu().numpy(), big[k][:n].cpu().numpy(),
+                              equal_nan=True), k
+    return {k: v.cpu().numpy() for k, v in small.items()}
+
+
+def lane_states(P, O, name, n):
+    if name == "hh":  # E = 0.2: some orbits escape
+        rng = np.random.default_rng(8)
+        x, m = O.hh_points(0.2, rng.uniform(-0.3, 0.6, 2 * n), rng.uniform(-0.4, 0.4, 2 * n))
+        return P.henon_heiles(), x[m == 1][:n]
+    if name.startswith("quartic"):
+        N = int(name[-1])
+        return P.quartic(N, 0.1), O.quartic_ic(O.quartic(N, 0.1), S.quartic_draws(9, n, N))
+    if name == "harmonic2":
+        return P.harmonic([1.0, 1.3]), np.random.default_rng(3).normal(size=(n, 4))
+    return P.double_pendulum(0.7, 2.5), S.dp_states(4, n, np.pi, 1.0)
+
+
+@pytest.mark.parametrize("integ", ["dop853", "dop853_adaptive"])
+@pytest.mark.parametrize("name", ["hh", "quartic1", "quartic3", "harmonic2", "dp"])
+def test_four_lanes_per_orbit(env, name, integ):
+    torch, P, O = env
+    n = 77  # the last wavefront holds 13 orbits of 16
+    print(f"case: four lanes per orbit {name} {integ}", flush=True)
+    sys_, x0 = lane_states(P, O, name, n)
+    for ind, K in ((O.IND_SALI | O.IND_LD | O.IND_ENERGY, 7), (O.IND_GALI, 10)):
+        kw = dict(dt=0.05, T=15.0, indicators=ind, integrator=integ, renorm_every=K,
+                  escape_r2=4.0 if name == "hh" else 0.0)
+        if ind & O.IND_SALI:
+            kw.update(early_exit=True, sali_threshold=0.02)
+        g = compare(env, sys_, x0, 33000, 2, **kw)
+        if name == "hh" and ind & O.IND_SALI:
+            assert {O.ST_ESCAPED, O.ST_EXITED} <= set(g["status"].tolist())
