@@ -19,6 +19,11 @@ namespace chx {
 // (fput_crow_rk.hip, fput_crow_rka.hip).
 hipError_t launch_fput_crow_rk(int ndof, int M, bool adaptive, const StepArgs &a,
                                hipStream_t s);
+// FPU chains of small ensembles, a row per vector (fput_split*.hip)
+bool fput_split_wanted(const StepArgs &a);
+hipError_t launch_fput_split(int ndof, const StepArgs &a, hipStream_t s);
+hipError_t launch_fput_split_rk(int ndof, const StepArgs &a, hipStream_t s);
+hipError_t launch_fput_split_rka(int ndof, const StepArgs &a, hipStream_t s);
 // LDS per block of four orbits of the DOP853 FPU kernels with more than four
 // vectors (fput_crow_rkl.hip)
 size_t fput_rkl_lds_bytes(int M, bool adaptive);
@@ -418,7 +423,13 @@ chx_status advance(chx_ensemble *e, int64_t s_end) {
                           ? custom_launch(e->custom, e->kind == CHX_SYS_CUSTOM_GENERAL, pl, a,
                                           e->block, e->stream)
                       : (e->kind == CHX_SYS_FPUT)
-                          ? (pl.o.integrator != CHX_INT_YOSHIDA4
+                          ? (fput_split_wanted(a)
+                                 ? (pl.o.integrator == CHX_INT_YOSHIDA4
+                                        ? launch_fput_split(pl.N, a, e->stream)
+                                    : pl.o.integrator == CHX_INT_DOP853
+                                        ? launch_fput_split_rk(pl.N, a, e->stream)
+                                        : launch_fput_split_rka(pl.N, a, e->stream))
+                             : pl.o.integrator != CHX_INT_YOSHIDA4
                                  ? launch_fput_crow_rk(pl.N, pl.M,
                                                        pl.o.integrator == CHX_INT_DOP853_ADAPTIVE,
                                                        a, e->stream)

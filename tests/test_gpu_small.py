@@ -74,3 +74,19 @@ def test_four_lanes_per_orbit(env, name, integ):
         g = compare(env, sys_, x0, 33000, 2, **kw)
         if name == "hh" and ind & O.IND_SALI:
             assert {O.ST_ESCAPED, O.ST_EXITED} <= set(g["status"].tolist())
+
+
+@pytest.mark.parametrize("integ", ["yoshida4", "dop853", "dop853_adaptive"])
+@pytest.mark.parametrize("N,m", [(2, 2), (5, 3), (11, 4), (15, 2), (16, 4)])
+def test_row_per_vector(env, N, m, integ):
+    torch, P, O = env
+    n = 37  # two orbits per wavefront leave half of the last one
+    print(f"case: a row per vector N={N} m={m} {integ}", flush=True)
+    x0 = O.fput_ic(O.fput(N), S.fput_mode_draws(40 + N, n))
+    e = np.quantile(np.sum(x0[:, :N] ** 2, axis=1), 0.8)
+    for ind in (O.IND_GALI | O.IND_SALI | O.IND_LD | O.IND_ENERGY, O.IND_GALI):
+        kw = dict(dt=0.05, T=12.0, indicators=ind, gali_kmax=m, integrator=integ, renorm_every=7,
+                  escape_r2=float(e) if ind & O.IND_SALI else 0.0)
+        if ind & O.IND_SALI:
+            kw.update(early_exit=True, sali_threshold=0.3)
+        compare(env, P.fput(N), x0, 2100, m, **kw)
