@@ -139,21 +139,22 @@ hipError_t batch_grad(chx_gate *g, const Acts &a, int B, const float *feat, cons
   float *gr = g->g;
   hipError_t e;
   if ((e = mlp_train_rows(r, B, s))) return e;
-  if ((e = mlp_bias_grad(a.bpart, B / 16, gr, loss_sum, s))) return e;
-  // weight gradients A^T dZ, layer 3, 2, 1, their parts left for mlp_grad_step
-  gp->w1 = a.work1;
-  gp->w2 = a.work2;
-  gp->w3 = a.work3;
-  // (the row kernel's outputs are feature-major with row stride B, so both
-  // operands run along K = rows)
-  if ((e = mlp_gemm(a.A2b, B, 1, a.dZ3b, 1, B, gr + MLP_W3, MLP_OUTP, MLP_H, MLP_OUTP, B, s,
-                    a.work3, MLP_SPLITK_WORK_SMALL, &gp->s3)))
-    return e;
-  if ((e = mlp_gemm(a.A1b, B, 1, a.dZ2b, 1, B, gr + MLP_W2, MLP_H, MLP_H, MLP_H, B, s,
-                    a.work2, MLP_SPLITK_WORK, &gp->s2)))
-    return e;
-  return mlp_gemm(a.X, B, 1, a.dZ1b, 1, B, gr + MLP_W1, MLP_H, MLP_INP, MLP_H, B, s,
-                  a.work1, MLP_SPLITK_WORK_SMALL, &gp->s1);
+  // weight gradients A^T dZ (the row kernel's outputs are feature-major with
+  // row stride B, so both operands run along the rows), their parts left
+  // for mlp_grad_step
+  BatchGrads b{};
+  b.w1 = {a.X, a.dZ1b, gr + MLP_W1, a.work1, MLP_SPLITK_WORK_SMALL, MLP_INP, MLP_H, 0, 0, 0};
+  b.w2 = {a.A1b, a.dZ2b, gr + MLP_W2, a.work2, MLP_SPLITK_WORK, MLP_H, MLP_H, 0, 0, 0};
+  b.w3 = {a.A2b, a.dZ3b, gr + MLP_W3, a.work3, MLP_SPLITK_WORK_SMALL, MLP_H, MLP_OUTP, 0, 0, 0};
+  b.ld = B;
+  b.K = B;
+  b.bpart = a.bpart;
+  b.nblk = B / 16;
+  b.grad = gr;
+  b.loss_sum = loss_sum;
+  if ((e = mlp_batch_grads(b, s))) return e;
+  *gp = {a.work1, a.work2, a.work3, b.w1.S, b.w2.S, b.w3.S};
+  return hipSuccess;
 }
 
 uint64_t mix64(uint64_t z) {

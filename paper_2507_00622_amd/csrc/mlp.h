@@ -32,13 +32,6 @@ constexpr int64_t MLP_F_W3 = MLP_F_W2T + (int64_t)MLP_H * MLP_H;     // W3, forw
 constexpr int64_t MLP_F_W3T = MLP_F_W3 + (int64_t)MLP_H * MLP_OUTP;  // W3, backward
 constexpr int64_t MLP_NFRAG = MLP_F_W3T + (int64_t)MLP_H * MLP_OUTP;
 
-// C = A B: BF16 operands at any strides, FP32 result.  With work (work_len
-// floats) and parts given (ldc == N) a product split over K leaves its parts
-// in work[z][M][N] for the caller to add and *parts = S (the number of
-// parts); with *parts == 1 the product is in C.
-hipError_t mlp_gemm(const uint16_t *A, int64_t a_r, int64_t a_c, const uint16_t *B, int64_t b_r,
-                    int64_t b_c, float *C, int64_t ldc, int M, int N, int K, hipStream_t s,
-                    float *work = nullptr, int64_t work_len = 0, int *parts = nullptr);
 // Split-K workspaces of the training pass (floats): up to 32 parts of the
 // 256 x 256 weight gradient, 64 of the 16 x 256 and 256 x 16 ones
 constexpr int64_t MLP_SPLITK_WORK = (int64_t)32 * MLP_H * MLP_H;
@@ -50,7 +43,7 @@ constexpr int64_t MLP_SPLITK_WORK_SMALL = (int64_t)64 * MLP_H * MLP_OUTP;
 // gradients; X, A1, A2, dZ3, dZ2, dZ1 (BF16, feature-major: row r of
 // feature j at j ld + r, ld >= B a multiple of 16) are left for the weight
 // gradients and each 16-row block's column sums of dZ1 | dZ2 | dZ3 and its
-// loss in bpart[B / 16][MLP_BIAS_COLS] for mlp_bias_grad.  pbF: the weights' BF16
+// loss in bpart[B / 16][MLP_BIAS_COLS] for mlp_batch_grads.  pbF: the weights' BF16
 // copy in MFMA operand order (mlp_weights_bf16).
 struct MlpRowsArgs {
   int64_t n, start, ld;
@@ -64,10 +57,30 @@ struct MlpRowsArgs {
   float *bpart;
 };
 hipError_t mlp_train_rows(const MlpRowsArgs &r, int B, hipStream_t s);
-// grad's b1, b2, b3 = the sums of the nblk blocks' partials (in order);
-// their loss sum is added to *loss_sum (if not null)
-hipError_t mlp_bias_grad(const float *bpart, int nblk, float *grad, float *loss_sum,
-                         hipStream_t s);
+// One weight gradient C[M][N] = sum over the batch's rows k of A[i][k] B[j][k]
+// (A, B feature-major, 16-byte aligned): (M, N) = (16, 256), (256, 256) or
+// (256, 16).  Split over K into S parts (set by mlp_batch_grads), part z in
+// work[z][M][N] for the caller to add in order; S = 1: the product is in C.
+struct WGrad {
+  const uint16_t *A, *B;
+  float *C, *work;
+  int64_t work_len;  // floats
+  int M, N;
+  int S, cpc, blocks;  // parts, 32-row chunks per part, blocks in the launch
+};
+// Every gradient of a batch whose rows mlp_train_rows left: the weights'
+// (K rows, feature stride ld), and grad's b1, b2, b3 = the sums of the nblk
+// blocks' partials (in order), their loss sum added to *loss_sum (if not
+// null).
+struct BatchGrads {
+  WGrad w1, w2, w3;
+  int64_t ld;
+  int K;
+  const float *bpart;
+  int nblk;
+  float *grad, *loss_sum;
+};
+hipError_t mlp_batch_grads(BatchGrads &b, hipStream_t s);
 hipError_t mlp_apply_mask(float *p, const uint8_t *mask, int64_t n, hipStream_t s);
 hipError_t mlp_fill(float *p, int64_t n, float v, hipStream_t s);
 hipError_t gate_select(int64_t n, const int *status, const int8_t *label1, const float *pc,

@@ -45,129 +45,65 @@ __device__ __forceinline__ float gelu_grad(float z) {
   return 0.5f * (1.0f + erf_scaled(z, e)) + z * 0.39894228040143268f * e;
 }
 
-// C[M][N] (fp32, row stride ldc) = A B,
-// A(i,k) = A[i*a_r + k*a_c], B(k,j) = B[k*b_r + j*b_c], both BF16; M, N, K
-// multiples of 16.  A block of 4 wavefronts computes a BM x BN tile of C,
-// (64, 64), (16, 64) or (64, 16) (rows past M are not stored).  K goes in
-// chunks of 32: the block stages the chunk of A (BM x 32) and of B
-// (32 x BN) in LDS with k contiguous (As[i][k], Bs[j][k], rows padded to
-// 40 elements against bank conflicts), reading global memory along
-// whichever index has unit stride, 8 elements (16 bytes) per load where VEC
-// says the addresses allow it, the next chunk's loads in flight during this
-// chunk's products; rows past M are staged as zeros, k past the end of the
-// block's K range is neither staged nor multiplied.  Each
-// wavefront takes its 16 x 16 tiles' fragments from LDS (4 consecutive k
+// One BM x BN tile of part z of a weight gradient C[M][N] = A B over the
+// batch's K rows: A(i, k) = A[i ld + k], B(k, j) = B[j ld + k], both BF16
+// and feature-major (rows contiguous), M, N, K and ld multiples of 16, FP32
+// accumulation.  A block of 4 wavefronts computes the tile, (64, 64), (16, 64)
+// or (64, 16).  K goes in chunks of 32: the block stages the chunk of A
+// (BM x 32) and of B (32 x BN) in LDS with k contiguous (As[i][k], Bs[j][k],
+// rows padded to 40 elements against bank conflicts), 8 elements (16 bytes)
+// per load, the next chunk's loads in flight during this chunk's
+// products; k past the end of the part is neither staged nor multiplied.
+// Each wavefront takes its 16 x 16 tiles' fragments from LDS (4 consecutive k
 // per lane, one 8-byte read) and issues v_mfma_f32_16x16x16bf16_1k per tile
 // and 16 k: lane l holds A[l % 16][4 (l / 16) + e], B[4 (l / 16) + e][l % 16]
-// and, after, D[4 (l / 16) + r][l % 16].  Split K: block z of gridDim.z
-// takes chunks [z cpc, (z + 1) cpc) and, when gridDim.z > 1, writes its
-// partial tile to work[z][M][N] for the caller to add in order of z. 
+// and, after, D[4 (l / 16) + r][l % 16].  Part z of S takes chunks
+// [z cpc, (z + 1) cpc) and, when S > 1, writes its partial tile to
+// work[z][M][N] for the caller to add in order of z, else to C.
 constexpr int GBK = 32, GPAD = GBK + 8;
 
-template <int BM, int BN, bool VEC>
-__global__ void __launch_bounds__(256) gemm_tile_kernel(const uint16_t *A, int64_t a_r,
-                                                        int64_t a_c, const uint16_t *B,
-                                                        int64_t b_r, int64_t b_c, float *C,
-                                                        int64_t ldc, int M, int N, int K,
-                                                        int cpc, float *work) {
+struct WGradLds {
+  uint16_t A[64][GPAD], B[64][GPAD];
+};
+
+template <int BM, int BN>
+__device__ __forceinline__ void wgrad_tile(const WGrad &g, int64_t ld, int K, int bx, int by,
+                                           int bz, WGradLds &lds) {
   // wavefronts: (64, 64) 2 x 2 of 2 x 2 tiles; (64, 16) 4 x 1 and (16, 64)
   // 1 x 4 of one tile
   constexpr int WGM = BM == 64 && BN == 64 ? 2 : (BM == 64 ? 4 : 1);
   constexpr int WGN = 4 / WGM;
   constexpr int TM = BM / (16 * WGM), TN = BN / (16 * WGN);
-  __shared__ __align__(16) uint16_t As[BM][GPAD];
-  __shared__ __align__(16) uint16_t Bs[BN][GPAD];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int wm = wave / WGN, wn = wave % WGN;
-  const int row0 = blockIdx.y * BM, col0 = blockIdx.x * BN;
-  const int kbeg = blockIdx.z * cpc * GBK;
-  const int kend = min(K, kbeg + cpc * GBK);
+  const int row0 = by * BM, col0 = bx * BN;
+  const int kbeg = bz * g.cpc * GBK;
+  const int kend = min(K, kbeg + g.cpc * GBK);
   const int li = lane & 15, lk = 4 * (lane >> 4);
   float4_t acc[TM][TN];
 #pragma unroll
   for (int a = 0; a < TM; ++a)
 #pragma unroll
     for (int b = 0; b < TN; ++b) acc[a][b] = (float4_t){0.f, 0.f, 0.f, 0.f};
-  // Runs of 8 elements of the A chunk and of the B chunk, run t of A being
-  // (i, kk) along k when a_c == 1, else along i (B alike: (j, kk) along k
-  // when b_r == 1, else along j); thread tid takes runs tid, tid + 256, ...
-  // M and K are multiples of 16 and runs start at multiples of 8, so a run
-  // is wholly inside or wholly outside the matrix.
+  // run t of 8 elements of a chunk: feature t / 4, rows 8 (t % 4) ..; thread
+  // tid takes runs tid, tid + 256, ...  K is a multiple of 16, so a run is
+  // wholly inside or wholly outside the part.
   constexpr int RA = BM * GBK / 8, RB = BN * GBK / 8;
-  constexpr int NA = (RA + 255) / 256, NB = (RB + 255) / 256;
-  const bool a_k = a_c == 1, b_k = b_r == 1;
-  const int64_t a_step = a_k ? 1 : a_r, b_step = b_k ? 1 : b_c;
-  auto run_a = [&](int q, int &i, int &k) {
-    const int t = tid + 256 * q;
-    i = a_k ? t / (GBK / 8) : (t % (BM / 8)) * 8;
-    k = a_k ? (t % (GBK / 8)) * 8 : t / (BM / 8);
-  };
-  auto run_b = [&](int q, int &j, int &k) {
-    const int t = tid + 256 * q;
-    j = b_k ? t / (GBK / 8) : (t % (BN / 8)) * 8;
-    k = b_k ? (t % (GBK / 8)) * 8 : t / (BN / 8);
-  };
-  auto load_run = [](const uint16_t *src, int64_t step, bool vec) {
-    uint4 v;
-    if (vec && step == 1) {
-      v = *(const uint4 *)src;
-    } else {
-      uint16_t *h = (uint16_t *)&v;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) h[e] = src[(int64_t)e * step];
-    }
-    return v;
-  };
-  uint4 va[NA], vb[NB];
-  // every run of the chunk at k0 goes out before any is waited for
+  static_assert(RA <= 256 && RB <= 256, "one run per thread");
+  const int i = tid / (GBK / 8), k = (tid % (GBK / 8)) * 8;
+  const bool ha = tid < RA, hb = tid < RB;
+  const uint16_t *pa = g.A + (int64_t)(row0 + i) * ld + k;
+  const uint16_t *pb = g.B + (int64_t)(col0 + i) * ld + k;
+  uint4 va, vb;
   auto load = [&](int k0) {
-#pragma unroll
-    for (int q = 0; q < NA; ++q) {
-      int i, k;
-      run_a(q, i, k);
-      va[q] = (tid + 256 * q < RA && row0 + i < M && k0 + k < kend)
-                  ? load_run(A + (int64_t)(row0 + i) * a_r + (int64_t)(k0 + k) * a_c, a_step, VEC)
-                  : make_uint4(0, 0, 0, 0);
-    }
-#pragma unroll
-    for (int q = 0; q < NB; ++q) {
-      int j, k;
-      run_b(q, j, k);
-      vb[q] = (tid + 256 * q < RB && k0 + k < kend)
-                  ? load_run(B + (int64_t)(k0 + k) * b_r + (int64_t)(col0 + j) * b_c, b_step, VEC)
-                  : make_uint4(0, 0, 0, 0);
-    }
+    const bool in = k0 + k < kend;
+    va = ha && in ? *(const uint4 *)(pa + k0) : make_uint4(0, 0, 0, 0);
+    vb = hb && in ? *(const uint4 *)(pb + k0) : make_uint4(0, 0, 0, 0);
   };
   load(kbeg);
   for (int k0 = kbeg; k0 < kend; k0 += GBK) {
-#pragma unroll
-    for (int q = 0; q < NA; ++q) {
-      if (tid + 256 * q >= RA) continue;
-      int i, k;
-      run_a(q, i, k);
-      if (k0 + k >= kend) continue;
-      if (a_k) {
-        *(uint4 *)&As[i][k] = va[q];
-      } else {
-        const uint16_t *h = (const uint16_t *)&va[q];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) As[i + e][k] = h[e];
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < NB; ++q) {
-      if (tid + 256 * q >= RB) continue;
-      int j, k;
-      run_b(q, j, k);
-      if (k0 + k >= kend) continue;
-      if (b_k) {
-        *(uint4 *)&Bs[j][k] = vb[q];
-      } else {
-        const uint16_t *h = (const uint16_t *)&vb[q];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) Bs[j + e][k] = h[e];
-      }
-    }
+    if (ha) *(uint4 *)&lds.A[i][k] = va;
+    if (hb) *(uint4 *)&lds.B[i][k] = vb;
     __syncthreads();
     // the next chunk's loads go out before this chunk's products
     if (k0 + GBK < kend) load(k0 + GBK);
@@ -179,10 +115,10 @@ __global__ void __launch_bounds__(256) gemm_tile_kernel(const uint16_t *A, int64
       short4_t af[TM], bfr[TN];
 #pragma unroll
       for (int a = 0; a < TM; ++a)
-        af[a] = *(const short4_t *)&As[(wm * TM + a) * 16 + li][kk + lk];
+        af[a] = *(const short4_t *)&lds.A[(wm * TM + a) * 16 + li][kk + lk];
 #pragma unroll
       for (int b = 0; b < TN; ++b)
-        bfr[b] = *(const short4_t *)&Bs[(wn * TN + b) * 16 + li][kk + lk];
+        bfr[b] = *(const short4_t *)&lds.B[(wn * TN + b) * 16 + li][kk + lk];
 #pragma unroll
       for (int a = 0; a < TM; ++a)
 #pragma unroll
@@ -191,27 +127,15 @@ __global__ void __launch_bounds__(256) gemm_tile_kernel(const uint16_t *A, int64
     }
     __syncthreads();
   }
-  if (gridDim.z > 1) {
-#pragma unroll
-    for (int a = 0; a < TM; ++a)
-#pragma unroll
-      for (int b = 0; b < TN; ++b)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int i = row0 + (wm * TM + a) * 16 + lk + r, j = col0 + (wn * TN + b) * 16 + li;
-          if (i < M) work[((int64_t)blockIdx.z * M + i) * N + j] = acc[a][b][r];
-        }
-    return;
-  }
+  float *out = g.S > 1 ? g.work + (int64_t)bz * g.M * g.N : g.C;
 #pragma unroll
   for (int a = 0; a < TM; ++a)
 #pragma unroll
     for (int b = 0; b < TN; ++b)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = row0 + (wm * TM + a) * 16 + lk + r, j = col0 + (wn * TN + b) * 16 + li;
-        if (i < M) C[(int64_t)i * ldc + j] = acc[a][b][r];
-      }
+      for (int r = 0; r < 4; ++r)
+        out[(int64_t)(row0 + (wm * TM + a) * 16 + lk + r) * g.N + col0 + (wn * TN + b) * 16 + li] =
+            acc[a][b][r];
 }
 
 // t = t + p[0] + p[stride] + ... + p[(count - 1) stride], added in that
@@ -286,9 +210,9 @@ __device__ __forceinline__ void mlp_fpos(int64_t i, int64_t &f0, int64_t &f1) {
 // the 256-wide layers (TR_T 16 x 16 tiles) and keeps Z1, Z2 in registers;
 // the activation entering each product waits in LDS (16 x 256 BF16).  The
 // weights come from the operand-order BF16 copy pbF, one coalesced 8-byte
-// load per lane and operand; the MFMAs run over k in ascending order as in
-// gemm_tile_kernel, so the products equal those of separate
-// gemm_tile_kernel launches bit for bit.  Block barriers wait for LDS only.
+// load per lane and operand; the MFMAs run over k in ascending order with
+// one accumulator, so the products equal those of separate launches bit for
+// bit.  Block barriers wait for LDS only.
 // The logits and the softmax are the first wavefront's.  Outputs for
 // the weight gradients: X, A1, A2, dZ3, dZ2, dZ1 (BF16) feature-major,
 // element (row r, feature j) at j ld + r, so that the weight-gradient
@@ -626,15 +550,14 @@ __global__ void __launch_bounds__(64 * TR_W, 4)
 }
 
 // Bias gradients and loss from the blocks' sums of train_rows_kernel:
-// column col of bpart[nblk][MLP_BIAS_COLS] summed over the blocks; thread
+// columns 16 cb .. of bpart[nblk][MLP_BIAS_COLS] summed over the blocks; thread
 // group g of a block of 256 adds blocks g, g + 16, g + 32, ... in order,
 // then the 16 group sums are added in order.  Columns 0..255 go to b1,
 // 256..511 to b2, 512..527 to b3, the loss column is added to *loss_sum.
-__global__ void __launch_bounds__(256) bias_grad_kernel(const float *bpart, int nblk,
-                                                        float *grad, float *loss_sum) {
-  __shared__ float red[16][17];
+__device__ __forceinline__ void bias_grad(const float *bpart, int nblk, float *grad,
+                                          float *loss_sum, int cb, float (*red)[17]) {
   const int c = threadIdx.x & 15, g = threadIdx.x >> 4;
-  const int col = blockIdx.x * 16 + c;
+  const int col = cb * 16 + c;
   const int cnt = g < nblk ? (nblk - g + 15) / 16 : 0;
   red[g][c] = ordered_sum<>(0.f, bpart + (int64_t)g * MLP_BIAS_COLS + col,
                           (int64_t)16 * MLP_BIAS_COLS, cnt);
@@ -651,6 +574,35 @@ __global__ void __launch_bounds__(256) bias_grad_kernel(const float *bpart, int 
       *loss_sum += t;
     }
   }
+}
+
+// Every parameter gradient of a batch in one launch, the kinds side by
+// side: the three weight gradients' tiles and parts, then the bias columns.
+// Each is a latency-bound trickle on its own (a part of W2's gradient is 4
+// chunks deep), so in a row they cost their sum, 24 us at batch 4096, and
+// together little more than the longest.
+__global__ void __launch_bounds__(256) batch_grads_kernel(const BatchGrads b) {
+  __shared__ __align__(16) union {
+    WGradLds w;
+    float red[16][17];
+  } lds;
+  int x = blockIdx.x;
+  if (x < b.w2.blocks) {  // 256 x 256: 4 x 4 tiles
+    wgrad_tile<64, 64>(b.w2, b.ld, b.K, x & 3, (x >> 2) & 3, x >> 4, lds.w);
+    return;
+  }
+  x -= b.w2.blocks;
+  if (x < b.w3.blocks) {  // 256 x 16: 4 tiles
+    wgrad_tile<64, 16>(b.w3, b.ld, b.K, 0, x & 3, x >> 2, lds.w);
+    return;
+  }
+  x -= b.w3.blocks;
+  if (x < b.w1.blocks) {  // 16 x 256: 4 tiles
+    wgrad_tile<16, 64>(b.w1, b.ld, b.K, x & 3, 0, x >> 2, lds.w);
+    return;
+  }
+  x -= b.w1.blocks;
+  bias_grad(b.bpart, b.nblk, b.grad, b.loss_sum, x, lds.red);
 }
 
 __global__ void fill_f32_kernel(float *p, int64_t n, float v) {
@@ -869,58 +821,29 @@ inline unsigned nb(int64_t n, int t = 256) { return (unsigned)((n + t - 1) / t);
 
 }  // namespace
 
-hipError_t mlp_gemm(const uint16_t *A, int64_t a_r, int64_t a_c, const uint16_t *B, int64_t b_r,
-                    int64_t b_c, float *C, int64_t ldc, int M, int N, int K, hipStream_t s,
-                    float *work, int64_t work_len, int *parts) {
-  if (M <= 0 || N <= 0 || K <= 0 || M % 16 || N % 16 || K % 16) return hipErrorInvalidValue;
-  // (64, 64) tiles where N allows, (16, 64) for a 16-row product, else
-  // (64, 16)
-  const int BN = N % 64 == 0 ? 64 : 16;
-  const int BM = BN == 64 && M == 16 ? 16 : 64;
-  const int64_t gm = (M + BM - 1) / BM, gn = N / BN;
-  if (gm > 65535) return hipErrorInvalidValue;
-  // split K (a workspace given) until about 512 blocks (two per CU), each
-  // part at least two chunks
-  const int chunks = (K + GBK - 1) / GBK;
-  if ((work && !parts) || (parts && ldc != N)) return hipErrorInvalidValue;
-  int S = 1;
-  while (work && gm * gn * S < 512 && chunks >= 4 * S && (int64_t)2 * S * M * N <= work_len)
-    S *= 2;
-  const int cpc = (chunks + S - 1) / S;
-  // 16-byte loads when every run of 8 along the unit stride is aligned
-  auto al = [](const void *p, int64_t s1, int64_t s2) {
-    const int64_t st = s1 == 1 ? s2 : s1;
-    return ((uintptr_t)p % 16 == 0) && (st % 8 == 0);
-  };
-  const bool vec = al(A, a_r, a_c) && al(B, b_c, b_r);
-  const dim3 grid((unsigned)gn, (unsigned)gm, (unsigned)S);
-#define CHX_GEMM_GO(bm, bn, v)                                                                 \
-  hipLaunchKernelGGL((gemm_tile_kernel<bm, bn, v>), grid, dim3(256), 0, s, A, a_r, a_c, B,     \
-                     b_r, b_c, C, ldc, M, N, K, cpc, work)
-#define CHX_GEMM_LAUNCH(bm, bn)        \
-  do {                                 \
-    if (vec) CHX_GEMM_GO(bm, bn, true); \
-    else CHX_GEMM_GO(bm, bn, false);   \
-  } while (0)
-  if (BN == 16) CHX_GEMM_LAUNCH(64, 16);
-  else if (BM == 16) CHX_GEMM_LAUNCH(16, 64);
-  else CHX_GEMM_LAUNCH(64, 64);
-#undef CHX_GEMM_LAUNCH
-#undef CHX_GEMM_GO
-  if (parts) *parts = S;
+hipError_t mlp_batch_grads(BatchGrads &b, hipStream_t s) {
+  if (b.K <= 0 || b.K % 16 || b.ld % 16 || b.nblk <= 0) return hipErrorInvalidValue;
+  const int chunks = (b.K + GBK - 1) / GBK;
+  for (WGrad *g : {&b.w1, &b.w2, &b.w3}) {
+    if (((uintptr_t)g->A | (uintptr_t)g->B) % 16) return hipErrorInvalidValue;
+    const int tiles = ((g->M + 63) / 64) * ((g->N + 63) / 64);
+    // split K until about 512 blocks (two per CU), each part at least two
+    // chunks
+    g->S = 1;
+    while (tiles * g->S < 512 && chunks >= 4 * g->S &&
+           (int64_t)2 * g->S * g->M * g->N <= g->work_len)
+      g->S *= 2;
+    g->cpc = (chunks + g->S - 1) / g->S;
+    g->blocks = tiles * g->S;
+  }
+  const int grid = b.w1.blocks + b.w2.blocks + b.w3.blocks + MLP_BIAS_COLS / 16;
+  hipLaunchKernelGGL(batch_grads_kernel, dim3(grid), dim3(256), 0, s, b);
   return hipGetLastError();
 }
 
 hipError_t mlp_train_rows(const MlpRowsArgs &r, int B, hipStream_t s) {
   if (B <= 0 || B % 16) return hipErrorInvalidValue;
   hipLaunchKernelGGL(train_rows_kernel, dim3((unsigned)(B / 16)), dim3(64 * TR_W), 0, s, r);
-  return hipGetLastError();
-}
-hipError_t mlp_bias_grad(const float *bpart, int nblk, float *grad, float *loss_sum,
-                         hipStream_t s) {
-  if (nblk <= 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(bias_grad_kernel, dim3(MLP_BIAS_COLS / 16), dim3(256), 0, s, bpart, nblk,
-                     grad, loss_sum);
   return hipGetLastError();
 }
 hipError_t mlp_fill(float *p, int64_t n, float v, hipStream_t s) {
