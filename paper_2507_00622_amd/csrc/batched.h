@@ -10,7 +10,7 @@ struct Pool {
   StepArgs a;                 // the pool's ensemble (s_begin/s_end unused)
   int64_t *sdone;             // [pitch] steps done per orbit
   int64_t *queue;             // [qcap] circular queue of orbit indices
-  unsigned long long *ctr;    // head, tail, tail0, spare
+  unsigned long long *ctr;    // head, tail, tail0, steps done (statistics)
   int64_t qcap;
   int kind;                   // PoolKind
 };
@@ -28,6 +28,8 @@ bool pool_kind_of(int sys, int ndof, int M, int *kind);
 int pool_slot_width(int kind);  // lanes per orbit
 hipError_t launch_queue_init(int64_t *queue, int64_t n, unsigned long long *ctr,
                              int64_t *sdone, int64_t pitch, hipStream_t s);
+// *sum += p[0] + ... + p[n - 1]
+hipError_t launch_sum_i64(const int64_t *p, int64_t n, unsigned long long *sum, hipStream_t s);
 // one flip kernel then one persistent launch
 hipError_t launch_batched(const BatchArgs &b, int blocks, int threads, hipStream_t s);
 hipError_t batched_occupancy(int threads, int *blocks_per_cu);

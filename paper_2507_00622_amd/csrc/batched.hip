@@ -253,6 +253,16 @@ __global__ void queue_init_kernel(int64_t *queue, int64_t n, unsigned long long 
   }
 }
 
+// *sum += p[0] + ... + p[n - 1] (whole numbers: the order does not matter)
+__global__ void sum_i64_kernel(const int64_t *p, int64_t n, unsigned long long *sum) {
+  int64_t t = 0;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * blockDim.x)
+    t += p[i];
+  for (int off = 32; off > 0; off >>= 1) t += __shfl_down(t, off, 64);
+  if ((threadIdx.x & 63) == 0) atomicAdd(sum, (unsigned long long)t);
+}
+
 __global__ void fill_i64_kernel(int64_t *p, int64_t n, int64_t v) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = v;
@@ -281,6 +291,14 @@ hipError_t launch_queue_init(int64_t *queue, int64_t n, unsigned long long *ctr,
                      n, ctr);
   hipLaunchKernelGGL(fill_i64_kernel, dim3((unsigned)((pitch + 255) / 256)), dim3(256), 0, s,
                      sdone, pitch, (int64_t)0);
+  return hipGetLastError();
+}
+
+hipError_t launch_sum_i64(const int64_t *p, int64_t n, unsigned long long *sum, hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  const int64_t nb = (n + 1023) / 1024;
+  hipLaunchKernelGGL(sum_i64_kernel, dim3((unsigned)(nb < 256 ? nb : 256)), dim3(256), 0, s, p, n,
+                     sum);
   return hipGetLastError();
 }
 

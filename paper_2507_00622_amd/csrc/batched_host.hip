@@ -307,10 +307,30 @@ extern "C" chx_status chx_integrate_batched(const chx_batch_item *items, int32_t
   int bpc = 1;
   ok(batched_occupancy(best_threads, &bpc));
   if (bpc < 1) bpc = 1;
-  const int blocks = ncu * bpc;
-  const int waves = blocks * (best_threads / 64);
-  // waves per pool in proportion to its estimated GPU time
-  {
+  int blocks = ncu * bpc;
+  int waves = blocks * (best_threads / 64);
+  // An ensemble that needs fewer wavefronts than the chip holds gets a grid
+  // of just those, one share per pool: with more, whichever wavefronts pop
+  // first take the orbits, and three may share a SIMD while others idle
+  // (65,536 quartic orbits, 1,024 of 3,072 wavefronts, 40,000 steps: 45
+  // -> 31 ms).
+  int64_t need = 0;
+  std::vector<int64_t> nw(n_items);
+  for (int i = 0; i < n_items; ++i) {
+    const int per = 64 / pool_slot_width(kinds[i]);  // orbits per wavefront
+    nw[i] = (ens[i]->n_active + per - 1) / per;
+    need += nw[i];
+  }
+  if (need <= waves) {
+    const int wpb = best_threads / 64;
+    blocks = (int)((need + wpb - 1) / wpb);
+    if (blocks < 1) blocks = 1;
+    waves = blocks * wpb;
+    b.split[0] = 0;
+    for (int i = 0; i < n_items; ++i) b.split[i + 1] = b.split[i] + (int)nw[i];
+    b.split[n_items] = waves;
+  } else {
+    // waves per pool in proportion to its estimated GPU time
     std::vector<double> w(n_items);
     double tot = 0.0;
     for (int i = 0; i < n_items; ++i) {
@@ -325,7 +345,15 @@ extern "C" chx_status chx_integrate_batched(const chx_batch_item *items, int32_t
     }
     b.split[n_items] = waves;
   }
-  // steps per launch: about 200 ms of GPU time per launch
+  // Steps per launch: at most about 200 ms of GPU time, and at most 1/32 of
+  // the longest run of a system with a lane per orbit.  There a slot that
+  // exits early refills by itself, so orbits integrated to the end one after
+  // another end scattered over wavefronts that are mostly idle; short turns
+  // carry all orbits forward together and pack them anew (262,144
+  // Henon-Heiles, 65,536 quartic and 16,384 FPU orbits to T = 400: 130 ms at
+  // 51,260 steps per launch, 98 at 4,000, 93 at 2,000, 92 at 1,250, 106 at
+  // 500).  Rows refill four to a wavefront and move more state per turn: FPU
+  // chains alone take 21 ms in one turn, 26 in turns of 1/32.
   const int K = plans[0].K;
   int64_t budget = opt->steps_per_launch;
   if (budget <= 0) {
@@ -335,6 +363,10 @@ extern "C" chx_status chx_integrate_batched(const chx_batch_item *items, int32_t
       worst = fmax(worst, best_cost[i] * slots);
     }
     budget = worst > 0.0 ? (int64_t)(0.2 / worst) : 100000;
+    int64_t longest = 0;
+    for (int i = 0; i < n_items; ++i)
+      if (pool_slot_width(kinds[i]) == 1 && plans[i].n_total > longest) longest = plans[i].n_total;
+    if (longest > 0 && budget > longest / 32) budget = longest / 32;
   }
   budget = (budget / K) * K;
   if (budget < K) budget = K;
@@ -384,17 +416,15 @@ extern "C" chx_status chx_integrate_batched(const chx_batch_item *items, int32_t
   }
   // results: every orbit is final; the caller's stream waits for ours
   int64_t osteps[MAX_POOLS] = {0, 0, 0, 0};
-  for (int i = 0; i < n_items; ++i) {
-    chx_ensemble *e = ens[i];
-    if (e->n_active > 0) {
-      std::vector<int64_t> sd(e->n_active);
-      ok(hipMemcpyAsync(sd.data(), bufs[i].sdone, sizeof(int64_t) * e->n_active,
-                        hipMemcpyDeviceToHost, bs));
-      ok(hipStreamSynchronize(bs));
-      for (int64_t v : sd) osteps[i] += v;
-    }
-    e->s_done = e->pl.n_total;
+  if (stats) {
+    for (int i = 0; i < n_items; ++i)
+      if (ens[i]->n_active > 0)
+        ok(launch_sum_i64(bufs[i].sdone, ens[i]->n_active, ctr + 4 * i + 3, bs));
+    ok(hipMemcpyAsync(hc, ctr, sizeof hc, hipMemcpyDeviceToHost, bs));
+    ok(hipStreamSynchronize(bs));
+    for (int i = 0; i < n_items; ++i) osteps[i] = (int64_t)hc[4 * i + 3];
   }
+  for (auto *e : ens) e->s_done = e->pl.n_total;
   ok(hipEventRecord(ev, bs));
   ok(hipStreamWaitEvent(cs, ev, 0));
   for (int i = 0; i < n_items && he == hipSuccess && st == CHX_OK; ++i)
