@@ -76,6 +76,22 @@ def test_four_lanes_per_orbit(env, name, integ):
             assert {O.ST_ESCAPED, O.ST_EXITED} <= set(g["status"].tolist())
 
 
+@pytest.mark.parametrize("name", ["hh", "quartic1", "quartic3", "harmonic2"])
+def test_two_lanes_per_orbit(env, name):
+    torch, P, O = env
+    n = 77  # the last wavefront holds 13 orbits of 32
+    print(f"case: two lanes per orbit {name}", flush=True)
+    sys_, x0 = lane_states(P, O, name, n)
+    for ind, K in ((O.IND_SALI | O.IND_LD | O.IND_ENERGY, 7), (O.IND_GALI, 10)):
+        kw = dict(dt=0.02, T=15.0, indicators=ind, renorm_every=K,
+                  escape_r2=4.0 if name == "hh" else 0.0)
+        if ind & O.IND_SALI:
+            kw.update(early_exit=True, sali_threshold=0.02)
+        g = compare(env, sys_, x0, 33000, 2, **kw)
+        if name == "hh" and ind & O.IND_SALI:
+            assert {O.ST_ESCAPED, O.ST_EXITED} <= set(g["status"].tolist())
+
+
 @pytest.mark.parametrize("integ", ["yoshida4", "dop853", "dop853_adaptive"])
 @pytest.mark.parametrize("N,m", [(2, 2), (5, 3), (11, 4), (15, 2), (16, 4)])
 def test_row_per_vector(env, N, m, integ):
