@@ -107,27 +107,23 @@ chx_status check_system(const chx_system *sys) {
   return CHX_OK;
 }
 
-// Whether the SALI/GALI set is kept as coordinates in the frame of the
-// Lyapunov set (StepArgs::frame) instead of being integrated.  It needs the
-// full set (n_l = 2N, orthonormal after every checkpoint) and the fixed
-// step (the adaptive solver's error estimate takes in every vector).
+// Whether the SALI/GALI set is kept as coordinates in the frame of the full
+// Lyapunov set (StepArgs::frame) instead of being integrated: FPU chains of
+// N = 8 on the row-pair kernel.
 // The coordinates lose what the frame loses: its vectors come out of the
 // Gram-Schmidt orthonormal to 1e-16 times the stretching ratio of one
 // checkpoint interval.  With the step resolving the motion (rate times step
 // below about 0.3) K = 16 steps keep that below 1e-12; longer intervals
 // integrate the set.
+// N = 16 was tried: the product with R costs 528 of the 1,920 FMAs it saves per
+// checkpoint and lengthens the pivots' chain (20.3 against 19.5 to 20.4 ms
+// for 65,536 chains and 500 steps).  So were the lane kernels (Henon-Heiles
+// with every indicator 22.0 -> 19.0 ms): on orbits that pass the saddles
+// SALI falls below 1e-8 and comes back, which leaves 1e-7 of it to the
+// rounding of either form, and the two then differ by as much.
 int frame_of(const chx_system *sys, const Plan &p) {
-  const int N = p.N;
-  if (p.m_s < 2 || p.n_l != 2 * N || p.K > 16) return 0;
-  // FPU chains: the row-pair kernel of N = 8.  (N = 16 was tried: the product
-  // with R costs 528 of the 1,920 FMAs it saves per checkpoint, and with the
-  // coordinates in LDS the pivots' chain grows by more than that: 20.3 against
-  // 19.5 to 20.4 ms for 65,536 chains and 500 steps.)
-  if (sys->kind == CHX_SYS_FPUT)
-    return p.o.integrator == CHX_INT_YOSHIDA4 && N == 8 && p.m_s <= N;
-  if (p.o.integrator == CHX_INT_DOP853_ADAPTIVE) return 0;
-  // the lane kernels: the SALI pair, the square-root LD
-  return p.m_s == 2 && !((p.o.indicators & CHX_IND_LD) && p.o.ld_p != 0.5);
+  return sys->kind == CHX_SYS_FPUT && p.o.integrator == CHX_INT_YOSHIDA4 && p.N == 8 &&
+         p.n_l == 2 * p.N && p.m_s >= 2 && p.m_s <= p.N && p.K <= 16;
 }
 
 chx_status make_plan(const chx_system *sys, const chx_options *opt, Plan *p) {

@@ -195,17 +195,15 @@ std::string lib_dir() {
 }
 
 // "chx::lane_kernel<chx::SysCustom, M, GP, MS>" and the like
-std::string kernel_expr(int integrator, int M, bool gp, int m_s, int frame) {
+std::string kernel_expr(int integrator, int M, bool gp, int m_s) {
   char b[128];
   if (integrator == CHX_INT_YOSHIDA4) {
     const int ms = (!gp && M >= 2 && m_s == 2) ? 2 : -1;
-    snprintf(b, sizeof b, "chx::lane_kernel<chx::SysCustom, %d, %s, %d, %s>", M,
-             gp ? "true" : "false", ms, frame ? "true" : "false");
-  } else if (integrator == CHX_INT_DOP853) {
-    snprintf(b, sizeof b, "chx::lane_rk_kernel<chx::SysCustom, %d, %s, %s>", M,
-             gp ? "true" : "false", frame ? "true" : "false");
+    snprintf(b, sizeof b, "chx::lane_kernel<chx::SysCustom, %d, %s, %d>", M, gp ? "true" : "false",
+             ms);
   } else {
-    snprintf(b, sizeof b, "chx::lane_rka_kernel<chx::SysCustom, %d, %s>", M,
+    snprintf(b, sizeof b, "chx::%s<chx::SysCustom, %d, %s>",
+             integrator == CHX_INT_DOP853 ? "lane_rk_kernel" : "lane_rka_kernel", M,
              gp ? "true" : "false");
   }
   return b;
@@ -293,7 +291,7 @@ chx_status compile(const std::string &src, int ndof, bool general, const std::st
 chx_status custom_prepare(const std::string &src, int ndof, bool general, const Plan &pl,
                           void **handle) {
   const bool gp = (pl.o.indicators & CHX_IND_LD) && pl.o.ld_p != 0.5;
-  const std::string expr = kernel_expr(pl.o.integrator, pl.M, gp, pl.m_s, pl.frame);
+  const std::string expr = kernel_expr(pl.o.integrator, pl.M, gp, pl.m_s);
   const std::string key =
       std::to_string(ndof) + (general ? " general\n" : " separable\n") + expr + "\n" + src;
   std::lock_guard<std::mutex> lk(g_mu);

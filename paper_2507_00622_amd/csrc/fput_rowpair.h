@@ -63,7 +63,11 @@ __device__ __forceinline__ double grp_sum(double s) {
 }  // namespace fputpair
 
 // FR: slot 2 holds the SALI/GALI set's coordinates in the frame of the full
-// Lyapunov set (n_l = 2N; lane_kernel.h).  Pivot j of the Gram-Schmidt makes
+// Lyapunov set (n_l = 2N).  The tangent map is linear and the 2N vectors,
+// orthonormal after every checkpoint, span the tangent space: a vector that
+// is Q c at one checkpoint is (Phi Q) c = Q' (R c) at the next, with Q' R = Phi Q
+// the Gram-Schmidt that the checkpoint computes anyway; norms, SALI and GALI
+// are those of c, and Q = I at t = 0.  Pivot j of the Gram-Schmidt makes
 // coordinate j of every lane's vector, R_jj c_j + sum_{k>j} R_jk c_k, R_jk
 // coming from lane k of the own orbit's slot through the FMA's row_newbcast
 // operand: 272 half-row FMAs per checkpoint against 960 and the coefficients'

@@ -46,23 +46,9 @@ struct has_hamiltonian<S, std::void_t<decltype(&S::hamiltonian)>> : std::true_ty
 // it; MS = -1 reads it from the launch arguments.
 // CO: coherent loads and stores of the orbit's state (gld/gst), for the
 // persistent kernel.
-// FR: the SALI/GALI set in the frame of the Lyapunov set.  The tangent map
-// is linear and the 2N Lyapunov vectors, orthonormal after every checkpoint,
-// span the tangent space: a vector that is Q c at one checkpoint is
-// (Phi Q) c = Q' (R c) at the next, with Q' R = Phi Q the Gram-Schmidt that
-// the checkpoint computes anyway.  So w[0..MS-1] hold the coordinates c, no
-// kick or drift touches them, and a checkpoint multiplies them by the upper
-// triangular R; norms, SALI and GALI are those of c, Q' being orthonormal.
-// Q = I at t = 0, so the set starts as the caller's vectors.  Henon-Heiles
-// with SALI and four exponents integrates 4 vectors instead of 6, with the
-// FP64 ALU as the bound either way: a 992,552-orbit section, 3000 steps,
-// 22.0 -> 19.0 ms with Yoshida-4; 212,700 orbits, 1000 steps of DOP853 31.2 ->
-// 23.7 ms (5 passes a step instead of 7).
-template <class S, int M, bool GP, int MS = -1, bool CO = false, bool FR = false>
+template <class S, int M, bool GP, int MS = -1, bool CO = false>
 struct LaneOrbit {
   static constexpr int N = S::N, D = 2 * N, MM = (M > 0 ? M : 1);
-  static_assert(!FR || (MS > 0 && M == MS + D), "a frame is the full Lyapunov set");
-  static constexpr int V0 = FR ? MS : 0;  // first vector that is integrated
   static constexpr int UNROLL = (N == 2 && M >= 4) ? 2 : 1;
   double x[D], w[MM][D], gm[MM];
   int ge[MM];
@@ -118,7 +104,7 @@ struct LaneOrbit {
     double Hs[S::NH];
     S::hess_scaled(x, hk, Hs, a.prm);
 #pragma unroll
-    for (int v = V0; v < M; ++v) {
+    for (int v = 0; v < M; ++v) {
       double dq[N];
 #pragma unroll
       for (int r = 0; r < N; ++r) dq[r] = w[v][r];
@@ -143,7 +129,7 @@ struct LaneOrbit {
 #pragma unroll
     for (int r = 0; r < N; ++r) x[r] = __builtin_fma(c, x[N + r], x[r]);
 #pragma unroll
-    for (int v = V0; v < M; ++v)
+    for (int v = 0; v < M; ++v)
 #pragma unroll
       for (int r = 0; r < N; ++r) w[v][r] = __builtin_fma(c, w[v][N + r], w[v][r]);
   }
@@ -224,8 +210,7 @@ struct LaneOrbit {
     if (s2 < a.thr2 && __builtin_isnan(tch)) tch = t;
     return s2;
   }
-  // Lyapunov set: modified Gram-Schmidt in vector order; FR: with it
-  // c <- R c of the set's coordinates, column by column of R
+  // Lyapunov set: modified Gram-Schmidt in vector order
   __device__ __forceinline__ void gram_schmidt(int m_s) {
 #pragma unroll
     for (int q = 0; q < M; ++q) {
@@ -238,11 +223,6 @@ struct LaneOrbit {
             for (int c = 0; c < D; ++c) d = __builtin_fma(w[l][c], w[q][c], d);
 #pragma unroll
             for (int c = 0; c < D; ++c) w[q][c] = __builtin_fma(-d, w[l][c], w[q][c]);
-            if constexpr (FR) {
-#pragma unroll
-              for (int v = 0; v < MS; ++v)
-                w[v][l - MS] = __builtin_fma(d, w[v][q - MS], w[v][l - MS]);
-            }
           }
         }
         double r2 = 0.0;
@@ -252,11 +232,6 @@ struct LaneOrbit {
 #pragma unroll
         for (int c = 0; c < D; ++c) w[q][c] *= inv;
         grow(gm[q], ge[q], r2);
-        if constexpr (FR) {
-          const double rq = rsqrt_inverse(r2, inv);
-#pragma unroll
-          for (int v = 0; v < MS; ++v) w[v][q - MS] *= rq;
-        }
       }
     }
   }
@@ -281,15 +256,9 @@ struct LaneOrbit {
       escaped = r2 > a.escape_r2;
     }
     double s2 = 0.0;
-    if constexpr (FR) {  // the set's coordinates follow from the Gram-Schmidt
-      gram_schmidt(m_s);
-      unit_set(m_s);
-      if (do_sali) s2 = sali(a, t);
-    } else {
-      unit_set(m_s);
-      if (do_sali) s2 = sali(a, t);
-      gram_schmidt(m_s);
-    }
+    unit_set(m_s);
+    if (do_sali) s2 = sali(a, t);
+    gram_schmidt(m_s);
     if (a.ind & CHX_IND_ENERGY) {
       double e;
       if constexpr (has_hamiltonian<S>::value) {
@@ -314,12 +283,12 @@ struct LaneOrbit {
   }
 };
 
-template <class S, int M, bool GP, int MS, bool FR = false>
+template <class S, int M, bool GP, int MS>
 __global__ void __launch_bounds__(256) lane_kernel(const StepArgs a) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= a.n) return;
   if (a.st[i] != CHX_ORBIT_OK) return;
-  LaneOrbit<S, M, GP, MS, false, FR> o;
+  LaneOrbit<S, M, GP, MS> o;
   o.load(a, i);
   const StepCoef k(a.dt);
   int64_t s = a.s_begin;
@@ -347,13 +316,6 @@ struct LaneDispatch {
     if (m == M) {
       const bool gp = (a.ind & CHX_IND_LD) && a.ld_p != 0.5;
       const int64_t grid = (a.n + block - 1) / block;
-      if constexpr (M == 2 + 2 * S::N) {
-        if (a.frame) {
-          hipLaunchKernelGGL((lane_kernel<S, M, false, 2, true>), dim3((unsigned)grid),
-                             dim3(block), 0, s, a);
-          return hipGetLastError();
-        }
-      }
       if (gp)
         hipLaunchKernelGGL((lane_kernel<S, M, true, -1>), dim3((unsigned)grid), dim3(block), 0, s,
                            a);

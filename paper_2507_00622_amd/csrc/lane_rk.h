@@ -47,11 +47,9 @@ constexpr int rec_width() {
     return S::N;
 }
 
-// FR: the SALI pair in the frame of the full Lyapunov set (LaneOrbit): the
-// vector passes are those of the Lyapunov set alone.
-template <class S, int M, bool GP, bool FR = false>
-struct RKOrbit : LaneOrbit<S, M, GP, (FR ? 2 : -1), false, FR> {
-  using Base = LaneOrbit<S, M, GP, (FR ? 2 : -1), false, FR>;
+template <class S, int M, bool GP>
+struct RKOrbit : LaneOrbit<S, M, GP, -1> {
+  using Base = LaneOrbit<S, M, GP, -1>;
   using Base::N;
   using Base::D;
   using Base::x;
@@ -229,7 +227,7 @@ struct RKOrbit : LaneOrbit<S, M, GP, (FR ? 2 : -1), false, FR> {
     }
     __builtin_amdgcn_sched_barrier(0);
     // (a compile-time loop: the vectors must stay in registers)
-    dop853::static_for<Base::V0, M>([&](auto vc) {
+    dop853::static_for<0, M>([&](auto vc) {
       constexpr int v = decltype(vc)::value;
       double k[12][D];  // h f(dY_i) of vector v
       dop853::static_for<0, 12>([&](auto ic) {
@@ -318,12 +316,12 @@ struct RKOrbit : LaneOrbit<S, M, GP, (FR ? 2 : -1), false, FR> {
 // per thread.
 extern __shared__ double lane_rk_lds[];
 
-template <class S, int M, bool GP, bool FR = false>
+template <class S, int M, bool GP>
 __global__ void __launch_bounds__(256) lane_rk_kernel(const StepArgs a) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= a.n) return;
   if (a.st[i] != CHX_ORBIT_OK) return;
-  RKOrbit<S, M, GP, FR> o;
+  RKOrbit<S, M, GP> o;
   o.load(a, i);
   const bool do_ld = (a.ind & CHX_IND_LD) != 0;
   const double h = a.dt;
@@ -478,13 +476,6 @@ struct LaneRKDispatch {
           hipLaunchKernelGGL((lane_rka_kernel<S, M, false>), dim3((unsigned)grid), dim3(block),
                              lds, s, a);
       } else {
-        if constexpr (M == 2 + 2 * S::N) {
-          if (a.frame) {
-            hipLaunchKernelGGL((lane_rk_kernel<S, M, false, true>), dim3((unsigned)grid),
-                               dim3(block), lds, s, a);
-            return hipGetLastError();
-          }
-        }
         if (gp)
           hipLaunchKernelGGL((lane_rk_kernel<S, M, true>), dim3((unsigned)grid), dim3(block),
                              lds, s, a);

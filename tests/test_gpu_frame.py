@@ -3,8 +3,8 @@ set, against the same set integrated.
 
 A run with all 2N Lyapunov vectors and at most 16 steps per checkpoint keeps
 the set in the frame; the same run with 2N - 1 of them integrates it.  The
-state, the energy error, the LD and the exponents do not depend on the set and
-agree bit for bit; the set's growth, SALI and GALI differ by rounding only:
+state, the energy error and the exponents do not depend on the set and
+agree bit for bit; the set's growth and GALI differ by rounding only:
 each checkpoint adds a few 1e-16 times the stretching of its interval
 (below 10 here), so 30 checkpoints stay below 1e-12.
 """
@@ -14,7 +14,7 @@ import pytest
 import seeded_inputs as S
 
 pytestmark = pytest.mark.gpu
-N_ORB = 70  # more than a wavefront of lanes, not a multiple of a row block
+N_ORB = 70  # eight orbits to a wavefront, the last one not full
 
 
 @pytest.fixture(scope="module")
@@ -26,51 +26,24 @@ def env():
     return torch, P, O
 
 
-def states(P, O, name, N):
-    if name == "hh":
-        rng = np.random.default_rng(1)
-        x, m = O.hh_points(1.0 / 6.0, rng.uniform(-0.3, 0.5, 3 * N_ORB),
-                           rng.uniform(-0.3, 0.3, 3 * N_ORB))
-        return P.henon_heiles(), x[m == 1][:N_ORB]
-    if name == "quartic":
-        return P.quartic(N, 0.1), O.quartic_ic(O.quartic(N, 0.1), S.quartic_draws(2, N_ORB, N))
-    if name == "harmonic":
-        return (P.harmonic([1.0, 1.3, 0.7][:N]),
-                np.random.default_rng(3).normal(size=(N_ORB, 2 * N)))
-    if name == "dp":
-        return P.double_pendulum(), S.dp_states(4, N_ORB, np.pi, 1.0)
-    return P.fput(N), O.fput_ic(O.fput(N), S.fput_mode_draws(5, N_ORB))
-
-
-LANE = [("hh", 2), ("quartic", 1), ("quartic", 3), ("harmonic", 2)]
-
-
-@pytest.mark.parametrize("name,N,integ,K", [
-    *[(s, N, i, k) for s, N in LANE for i, k in (("yoshida4", 10), ("dop853", 10))],
-    ("hh", 2, "yoshida4", 1), ("hh", 2, "yoshida4", 16), ("hh", 2, "dop853", 16),
-    ("dp", 2, "dop853", 10), ("fput", 8, "yoshida4", 10), ("fput", 8, "yoshida4", 16)])
-def test_frame_against_integrated_set(env, name, N, integ, K):
+@pytest.mark.parametrize("K", [1, 10, 16])
+def test_frame_against_integrated_set(env, K):
     torch, P, O = env
-    print(f"case: frame {name} N={N} {integ} K={K}", flush=True)
-    sys_, x0 = states(P, O, name, N)
-    chain = name == "fput"
-    sets = (2, N // 2 + 1, N) if chain else (2,)
-    dt = 0.02
-    for m in sets:
-        # the chains' kernels take SALI with n_lyap a multiple of 16 only
-        ind = O.IND_GALI | O.IND_LYAP | O.IND_ENERGY
-        ind |= 0 if chain else O.IND_SALI | O.IND_LD
-        kw = dict(dt=dt, T=dt * (30 * K - (K > 1)), indicators=ind, gali_kmax=m,
-                  renorm_every=K, integrator=integ)
+    print(f"case: frame FPU N=8 K={K}", flush=True)
+    N, dt = 8, 0.02
+    x0 = O.fput_ic(O.fput(N), S.fput_mode_draws(5, N_ORB))
+    for m in (2, 5, 8):
+        # SALI needs n_lyap a multiple of 16 here, so GALI alone
+        kw = dict(dt=dt, T=dt * (30 * K - (K > 1)),
+                  indicators=O.IND_GALI | O.IND_LYAP | O.IND_ENERGY, gali_kmax=m, renorm_every=K)
         w0 = S.deviation_vectors(6, N_ORB, m, 2 * N)
         t = lambda a: torch.as_tensor(a, device="cuda:0")
-        a = P.integrate_ensemble(sys_, t(x0), w0=t(w0), n_lyap=2 * N, **kw)
-        b = P.integrate_ensemble(sys_, t(x0), w0=t(w0), n_lyap=2 * N - 1, **kw)
+        a = P.integrate_ensemble(P.fput(N), t(x0), w0=t(w0), n_lyap=2 * N, **kw)
+        b = P.integrate_ensemble(P.fput(N), t(x0), w0=t(w0), n_lyap=2 * N - 1, **kw)
         torch.cuda.synchronize()
         a, b = ({k: v.cpu().numpy() for k, v in r.items()} for r in (a, b))
-        for k in ("x_final", "t_end", "status", "energy_err") + (() if chain else ("ld", "label")):
+        for k in ("x_final", "t_end", "status", "energy_err"):
             assert np.array_equal(a[k], b[k]), k
         assert np.abs(a["lyap"][:, :-1] - b["lyap"]).max() < 1e-12
         assert np.abs(a["ln_growth"] - b["ln_growth"]).max() < 1e-12
-        for k in ("gali",) + (() if chain else ("sali_final", "sali_min")):
-            assert np.abs(a[k] - b[k]).max() < 1e-12, k
+        assert np.abs(a["gali"] - b["gali"]).max() < 1e-12
