@@ -44,6 +44,15 @@ __device__ __forceinline__ double sqrt_ld(double a) {
   return __builtin_fma(s, r, s);
 }
 
+// acc += sqrt(|a|) for the LD, of sqrt_ld's accuracy: s f with f = (3 - s y) / 2,
+// the sum taken by the last FMA (one instruction less than adding sqrt_ld).
+__device__ __forceinline__ void add_sqrt_ld(double a, double &acc) {
+  a = __builtin_fabs(a) + 1e-300;
+  const double y = __builtin_amdgcn_rsq(a);
+  const double s = a * y;
+  acc = __builtin_fma(s, __builtin_fma(-0.5, s * y, 1.5), acc);
+}
+
 // Step coefficients of one launch.
 struct StepCoef {
   double c0, c1, hk0, hk1, hkm, hdt;

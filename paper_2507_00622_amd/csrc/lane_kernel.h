@@ -139,9 +139,16 @@ struct LaneOrbit {
     else
       return sqrt_ld(u);
   }
+  // acc += |u|^p
+  __device__ __forceinline__ void ld_add(const StepArgs &a, double u, double &acc) const {
+    if constexpr (GP)
+      acc += ld_term(a, u);
+    else
+      add_sqrt_ld(u, acc);
+  }
   // One step without its closing kicks: the state gets K(d3) (the LD needs
   // p at the endpoint), the vectors wait for the merged kick.
-  __device__ __forceinline__ void step_body(const StepArgs &a, const StepCoef &k, bool do_ld) {
+  __device__ __forceinline__ void step_body(const StepArgs &a, const StepCoef &k) {
     drift(k.c0);
     S::force(x, F, a.prm);
     kick_state(k.hk1);
@@ -153,17 +160,17 @@ struct LaneOrbit {
     drift(k.c0);
     S::force(x, F, a.prm);
     kick_state(k.hk0);  // p at the step endpoint
-    if (do_ld) {
-      double g = 0.0;
-#pragma unroll
-      for (int r = 0; r < N; ++r) g += ld_term(a, x[N + r]) + ld_term(a, F[r]);
-      ld = __builtin_fma(k.hdt, gprev + g, ld);
-      gprev = g;
-    }
   }
-  // blk whole steps from one checkpoint to the next
+  // blk whole steps from one checkpoint to the next.  The LD's trapezoid sum
+  // over them is dt (g_1 + ... + g_blk) + dt/2 (g_0 - g_blk): inside the block
+  // each root joins a running sum (the momenta's and the force's apart, as
+  // the two-lanes-per-orbit kernel holds them) and only the last
+  // integrand is formed, for the next block.  6 instructions per root, one of
+  // them v_rsq_f64, against 7.5 with an integrand per step: 8.5 million
+  // LD-only orbits, 2,000 steps, 35.2 -> 32.7 ms.
   __device__ void block(const StepArgs &a, const StepCoef &k, int blk) {
     const bool do_ld = (a.ind & CHX_IND_LD) != 0;
+    double sp = 0.0, sf = 0.0;
     kick_state(k.hk0);
     kick_vectors(a, k.hk0);
     // two steps per iteration saves register moves of the loop-carried
@@ -171,12 +178,35 @@ struct LaneOrbit {
     // occupancy
 #pragma unroll(UNROLL)
     for (int s = 0; s + 1 < blk; ++s) {
-      step_body(a, k, do_ld);
+      step_body(a, k);
+      if (do_ld) {
+#pragma unroll
+        for (int r = 0; r < N; ++r) {
+          ld_add(a, x[N + r], sp);
+          ld_add(a, F[r], sf);
+        }
+      }
       kick_state(k.hk0);  // first kick of the next step
       kick_vectors(a, k.hkm);
     }
-    step_body(a, k, do_ld);
+    step_body(a, k);
+    if (do_ld) {
+      double gp = 0.0, gf = 0.0;
+#pragma unroll
+      for (int r = 0; r < N; ++r) {
+        ld_add(a, x[N + r], gp);
+        ld_add(a, F[r], gf);
+      }
+      ld_block(a, k, sp + sf, gp + gf);
+    }
     kick_vectors(a, k.hk0);
+  }
+  // s: the integrands of the block's inner endpoints; g: of its last
+  __device__ __forceinline__ void ld_block(const StepArgs &a, const StepCoef &k, double s,
+                                           double g) {
+    ld = __builtin_fma(a.dt, s + g, ld);
+    ld = __builtin_fma(k.hdt, gprev - g, ld);
+    gprev = g;
   }
 
   // SALI/GALI set: each vector back to unit length

@@ -5,7 +5,8 @@
 // on its SIMD and paced by one lane's instruction stream (the state, two
 // vectors, the LD's 2N roots).  Here both lanes of a pair integrate the
 // state, lane v carries vector v, and each takes half of the LD's roots (lane
-// 0 those of the momenta, lane 1 those of the force), exchanged by DPP.  Every
+// 0 those of the momenta, lane 1 those of the force), their sums exchanged by
+// DPP once per checkpoint.  Every
 // value takes the operations of the one-lane kernel in their order: the
 // results have the same bits, so a subset of an ensemble may cross from one
 // kernel to the other.
@@ -55,39 +56,27 @@ struct PairOrbit : LaneOrbit<S, 1, false, -1> {
       a.st[i] = this->st;
     }
   }
-  __device__ __forceinline__ void step_body(const StepArgs &a, const StepCoef &k, bool do_ld) {
-    this->drift(k.c0);
-    S::force(x, F, a.prm);
-    this->kick_state(k.hk1);
-    this->kick_vectors(a, k.hk1);
-    this->drift(k.c1);
-    S::force(x, F, a.prm);
-    this->kick_state(k.hk1);
-    this->kick_vectors(a, k.hk1);
-    this->drift(k.c0);
-    S::force(x, F, a.prm);
-    this->kick_state(k.hk0);  // p at the step endpoint
-    if (do_ld) {
-      double g = 0.0;
-#pragma unroll
-      for (int r = 0; r < N; ++r) {
-        const double u = sqrt_ld(v == 0 ? x[N + r] : F[r]);
-        g += u + other(u);
-      }
-      this->ld = __builtin_fma(k.hdt, this->gprev + g, this->ld);
-      this->gprev = g;
-    }
-  }
   __device__ void block(const StepArgs &a, const StepCoef &k, int blk) {
     const bool do_ld = (a.ind & CHX_IND_LD) != 0;
+    double sum = 0.0;  // this lane's roots: the momenta's or the force's
     this->kick_state(k.hk0);
     this->kick_vectors(a, k.hk0);
     for (int s = 0; s + 1 < blk; ++s) {
-      step_body(a, k, do_ld);
+      Base::step_body(a, k);
+      if (do_ld) {
+#pragma unroll
+        for (int r = 0; r < N; ++r) add_sqrt_ld(v == 0 ? x[N + r] : F[r], sum);
+      }
       this->kick_state(k.hk0);  // first kick of the next step
       this->kick_vectors(a, k.hkm);
     }
-    step_body(a, k, do_ld);
+    Base::step_body(a, k);
+    if (do_ld) {
+      double g = 0.0;
+#pragma unroll
+      for (int r = 0; r < N; ++r) add_sqrt_ld(v == 0 ? x[N + r] : F[r], g);
+      this->ld_block(a, k, sum + other(sum), g + other(g));
+    }
     this->kick_vectors(a, k.hk0);
   }
   // Checkpoint at t (LaneOrbit::checkpoint); the decisions are taken on

@@ -15,7 +15,7 @@ hipError_t go(const StepArgs &a, hipStream_t s) {
 // wavefront of pairs per SIMD.  Measured, Henon-Heiles, 4,000 steps, one lane
 // against two: with energy n = 8,192 0.92 / 0.84 ms, 32,768 1.35 / 1.26,
 // 65,536 1.77 / 2.04; with the LD 1.21 / 1.07, 1.33 / 1.26, 1.43 / 1.95;
-// 796 orbits, LD, 20,000 steps 6.2 / 4.5 ms.
+// 796 orbits, LD, 20,000 steps 6.1 / 4.0 ms.
 bool lane_pair_wanted(const StepArgs &a) {
   return a.m_s == 2 && a.n_l == 0 && !((a.ind & CHX_IND_LD) && a.ld_p != 0.5) && a.n <= 32768;
 }
