@@ -190,7 +190,8 @@ __host__ __device__ __forceinline__ void sincos_cw(double x, double &s, double &
                                     __builtin_fma(k, 0x1.8a2e000000000p-81,
                                                   k * 0x1.b839a252049c1p-104));
   const double lo = (e1 + e2) - tail;
-  const double r = r2 + lo;
+  // an angle out of range: NaN from here on
+  const double r = __builtin_fabs(x) < 0x1p32 ? r2 + lo : __builtin_nan("");
   const double dr = lo - (r - r2);
   const double z = r * r;
   double ps = 0x1.952c77030ad4ap-49;  // 1/17!
@@ -213,12 +214,12 @@ __host__ __device__ __forceinline__ void sincos_cw(double x, double &s, double &
   const double hz = 0.5 * z, wz = 1.0 - hz;
   const double sr = r + __builtin_fma(r * z, ps, dr * wz);
   const double cr = wz + ((((1.0 - wz) - hz) + (z * z) * pc) - r * dr);
-  const long long kq = (__builtin_fabs(k) < 0x1p32) ? (long long)k : 0;
-  const int q = (int)(kq & 3);
+  // k mod 4 from the low bits of k + 1.5 2^52 (a conversion of k to an integer
+  // takes eight instructions), the signs by flipping the sign bits
+  const uint64_t q = __builtin_bit_cast(uint64_t, k + 0x1.8p52);
   const double a = (q & 1) ? cr : sr, b = (q & 1) ? sr : cr;
-  const bool ok = __builtin_fabs(x) < 0x1p32;
-  s = ok ? ((q & 2) ? -a : a) : __builtin_nan("");
-  c = ok ? (((q + 1) & 2) ? -b : b) : __builtin_nan("");
+  s = __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, a) ^ ((q & 2) << 62));
+  c = __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, b) ^ (((q + 1) & 2) << 62));
 }
 
 struct SysDP {
