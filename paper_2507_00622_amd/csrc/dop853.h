@@ -76,6 +76,52 @@ constexpr double FACC1 = 1.0 / 0.333;
 constexpr double FACC2 = 1.0 / 6.0;
 constexpr int MAX_ATTEMPTS = 100000;
 
+// The non-zero entries of A row by row, then those of B and of ER, in
+// constant memory.  As literals they take two scalar moves each, and hoisted
+// out of the step loop they overflow the scalar registers into lanes of
+// vector registers (v_writelane, then a v_readlane per use: 424 of the 3,900
+// instructions of a Henon-Heiles step with six vectors, beside 865 scalar
+// moves).  Read through a pointer that each pass makes opaque they come eight
+// to a scalar load and stay in the pass.
+constexpr int nonzero_before(int i, int j) {
+  int n = 0;
+  for (int r = 0; r < 12; ++r)
+    for (int c = 0; c < 12; ++c)
+      if ((r < i || (r == i && c < j)) && A[r][c] != 0.0) ++n;
+  return n;
+}
+constexpr int weights_before(const double (&w)[12], int j) {
+  int n = 0;
+  for (int c = 0; c < j; ++c)
+    if (w[c] != 0.0) ++n;
+  return n;
+}
+constexpr int AT_B = nonzero_before(12, 0), AT_ER = AT_B + weights_before(B, 12);
+constexpr int NCOEF = AT_ER + weights_before(ER, 12);
+struct CoefTable {
+  double v[NCOEF];
+};
+constexpr CoefTable coef_table() {
+  CoefTable t{};
+  int n = 0;
+  for (int r = 0; r < 12; ++r)
+    for (int c = 0; c < 12; ++c)
+      if (A[r][c] != 0.0) t.v[n++] = A[r][c];
+  for (int c = 0; c < 12; ++c)
+    if (B[c] != 0.0) t.v[n++] = B[c];
+  for (int c = 0; c < 12; ++c)
+    if (ER[c] != 0.0) t.v[n++] = ER[c];
+  return t;
+}
+static __constant__ const CoefTable COEF = coef_table();
+typedef const __attribute__((address_space(4))) double *Coef;
+// the table's address, for one pass
+__device__ __forceinline__ Coef coef() {
+  Coef p = (Coef)&COEF.v[0];
+  asm volatile("" : "+s"(p));
+  return p;
+}
+
 template <int I, int E, class Fn>
 __device__ __forceinline__ void static_for(Fn &&f) {
   if constexpr (I < E) {
@@ -86,29 +132,30 @@ __device__ __forceinline__ void static_for(Fn &&f) {
 
 // sum_{j<I} A[I][j] k[j][c] over the non-zero entries, in order of j
 template <int I, int D>
-__device__ __forceinline__ double stage_sum(const double (&k)[12][D], int c) {
+__device__ __forceinline__ double stage_sum(Coef cf, const double (&k)[12][D], int c) {
   double s = 0.0;
   static_for<0, I>([&](auto jc) {
     constexpr int J = decltype(jc)::value;
-    if constexpr (A[I][J] != 0.0) s = __builtin_fma(A[I][J], k[J][c], s);
+    if constexpr (A[I][J] != 0.0) s = __builtin_fma(cf[nonzero_before(I, J)], k[J][c], s);
   });
   return s;
 }
 template <int D>
-__device__ __forceinline__ double err5_sum(const double (&k)[12][D], int c) {
+__device__ __forceinline__ double err5_sum(Coef cf, const double (&k)[12][D], int c) {
   double s = 0.0;
   static_for<0, 12>([&](auto jc) {
     constexpr int J = decltype(jc)::value;
-    if constexpr (ER[J] != 0.0) s = __builtin_fma(ER[J], k[J][c], s);
+    if constexpr (ER[J] != 0.0)
+      s = __builtin_fma(cf[AT_ER + weights_before(ER, J)], k[J][c], s);
   });
   return s;
 }
 template <int D>
-__device__ __forceinline__ double final_sum(const double (&k)[12][D], int c) {
+__device__ __forceinline__ double final_sum(Coef cf, const double (&k)[12][D], int c) {
   double s = 0.0;
   static_for<0, 12>([&](auto jc) {
     constexpr int J = decltype(jc)::value;
-    if constexpr (B[J] != 0.0) s = __builtin_fma(B[J], k[J][c], s);
+    if constexpr (B[J] != 0.0) s = __builtin_fma(cf[AT_B + weights_before(B, J)], k[J][c], s);
   });
   return s;
 }
@@ -118,12 +165,12 @@ __device__ __forceinline__ double final_sum(const double (&k)[12][D], int c) {
 // e5 += (sum_i er_i k_i / sk)^2, e3 += ((sb - bhh . k_{1,9,12}) / sk)^2 with
 // sk = atol + rtol max(|y|, |yn|).
 template <int D2>
-__device__ __forceinline__ void err_terms(const double (&k)[12][D2], int c, double y, double yn,
+__device__ __forceinline__ void err_terms(Coef cf, const double (&k)[12][D2], int c, double y, double yn,
                                           double sb, double rtol, double atol, double &e5,
                                           double &e3) {
   const double sk = __builtin_fma(rtol, __builtin_fmax(__builtin_fabs(y), __builtin_fabs(yn)),
                                   atol);
-  const double r5 = err5_sum(k, c) / sk;
+  const double r5 = err5_sum(cf, k, c) / sk;
   const double s3 = sb - BHH1 * k[0][c] - BHH2 * k[8][c] - BHH3 * k[11][c];
   const double r3 = s3 / sk;
   e5 = __builtin_fma(r5, r5, e5);

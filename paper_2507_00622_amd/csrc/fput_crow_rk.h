@@ -38,13 +38,13 @@ struct CRowRK : CRowOrbit<N, M> {
 
   // the state's 12 stages: k = h f at Y = x + sum a_ij k_j; g += the LD
   // integrand of this lane's components at the weighted stages
-  __device__ __forceinline__ void state_pass(const StepArgs &a, double h, bool do_ld,
+  __device__ __forceinline__ void state_pass(const StepArgs &a, dop853::Coef cf, double h, bool do_ld,
                                              double (&kq)[12][1], double (&kp)[12][1],
                                              double &g) {
     dop853::static_for<0, 12>([&](auto ic) {
       constexpr int I = decltype(ic)::value;
-      const double Yq = q + dop853::stage_sum<I>(kq, 0);
-      const double Yp = p + dop853::stage_sum<I>(kp, 0);
+      const double Yq = q + dop853::stage_sum<I>(cf, kq, 0);
+      const double Yp = p + dop853::stage_sum<I>(cf, kp, 0);
       double F, kl, kr;
       B::spring_terms(a, Yq, mass, F, kl, kr);
       skl[I] = kl;
@@ -59,13 +59,13 @@ struct CRowRK : CRowOrbit<N, M> {
 
   // vector v's 12 stages from the state's stiffnesses
   template <int V>
-  __device__ __forceinline__ void vector_pass(double h, double (&kq)[12][1],
+  __device__ __forceinline__ void vector_pass(dop853::Coef cf, double h, double (&kq)[12][1],
                                               double (&kp)[12][1]) {
     using namespace fputrow;
     dop853::static_for<0, 12>([&](auto ic) {
       constexpr int I = decltype(ic)::value;
-      const double Yq = dq[V] + dop853::stage_sum<I>(kq, 0);
-      const double Yp = dp[V] + dop853::stage_sum<I>(kp, 0);
+      const double Yq = dq[V] + dop853::stage_sum<I>(cf, kq, 0);
+      const double Yp = dp[V] + dop853::stage_sum<I>(cf, kp, 0);
       const double ql = dpp<0x111>(Yq);  // row_shr:1
       const double qr = dpp<0x101>(Yq);  // row_shl:1
       double hq = (skl[I] + skr[I]) * Yq;
@@ -79,19 +79,21 @@ struct CRowRK : CRowOrbit<N, M> {
   // one fixed DOP853 step of size h
   __device__ __forceinline__ void rk_step(const StepArgs &a, double h, bool do_ld) {
     {
+      const dop853::Coef cf = dop853::coef();
       double kq[12][1], kp[12][1], g = 0.0;
-      state_pass(a, h, do_ld, kq, kp, g);
-      q += dop853::final_sum(kq, 0);
-      p += dop853::final_sum(kp, 0);
+      state_pass(a, cf, h, do_ld, kq, kp, g);
+      q += dop853::final_sum(cf, kq, 0);
+      p += dop853::final_sum(cf, kp, 0);
       if (do_ld) ld = __builtin_fma(h, fputrow::row_sum(g), ld);
     }
     __builtin_amdgcn_sched_barrier(0);
     dop853::static_for<0, M>([&](auto vc) {
       constexpr int V = decltype(vc)::value;
+      const dop853::Coef cf = dop853::coef();
       double kq[12][1], kp[12][1];
-      vector_pass<V>(h, kq, kp);
-      dq[V] += dop853::final_sum(kq, 0);
-      dp[V] += dop853::final_sum(kp, 0);
+      vector_pass<V>(cf, h, kq, kp);
+      dq[V] += dop853::final_sum(cf, kq, 0);
+      dp[V] += dop853::final_sum(cf, kp, 0);
       __builtin_amdgcn_sched_barrier(0);
     });
   }
@@ -105,28 +107,30 @@ struct CRowRK : CRowOrbit<N, M> {
                                                double (&dpn)[MM], double &ldn) {
     double e5 = 0.0, e3 = 0.0;
     {
+      const dop853::Coef cf = dop853::coef();
       double kq[12][1], kp[12][1], g = 0.0;
-      state_pass(a, h, do_ld, kq, kp, g);
-      const double sq = dop853::final_sum(kq, 0), sp = dop853::final_sum(kp, 0);
+      state_pass(a, cf, h, do_ld, kq, kp, g);
+      const double sq = dop853::final_sum(cf, kq, 0), sp = dop853::final_sum(cf, kp, 0);
       qn = q + sq;
       pn = p + sp;
       if (mass) {  // ghost lanes are no components (0 / 0 when atol = 0)
-        dop853::err_terms(kq, 0, q, qn, sq, a.rtol, a.atol, e5, e3);
-        dop853::err_terms(kp, 0, p, pn, sp, a.rtol, a.atol, e5, e3);
+        dop853::err_terms(cf, kq, 0, q, qn, sq, a.rtol, a.atol, e5, e3);
+        dop853::err_terms(cf, kp, 0, p, pn, sp, a.rtol, a.atol, e5, e3);
       }
       ldn = do_ld ? __builtin_fma(h, fputrow::row_sum(g), ld) : ld;
     }
     __builtin_amdgcn_sched_barrier(0);
     dop853::static_for<0, M>([&](auto vc) {
       constexpr int V = decltype(vc)::value;
+      const dop853::Coef cf = dop853::coef();
       double kq[12][1], kp[12][1];
-      vector_pass<V>(h, kq, kp);
-      const double sq = dop853::final_sum(kq, 0), sp = dop853::final_sum(kp, 0);
+      vector_pass<V>(cf, h, kq, kp);
+      const double sq = dop853::final_sum(cf, kq, 0), sp = dop853::final_sum(cf, kp, 0);
       dqn[V] = dq[V] + sq;
       dpn[V] = dp[V] + sp;
       if (mass) {
-        dop853::err_terms(kq, 0, dq[V], dqn[V], sq, a.rtol, a.atol, e5, e3);
-        dop853::err_terms(kp, 0, dp[V], dpn[V], sp, a.rtol, a.atol, e5, e3);
+        dop853::err_terms(cf, kq, 0, dq[V], dqn[V], sq, a.rtol, a.atol, e5, e3);
+        dop853::err_terms(cf, kp, 0, dp[V], dpn[V], sp, a.rtol, a.atol, e5, e3);
       }
       __builtin_amdgcn_sched_barrier(0);
     });

@@ -45,13 +45,13 @@ inline size_t lds_bytes(int M, bool adaptive) {
 // One vector's 12 stages from the state's stage stiffnesses (the same
 // arithmetic as the register form in fput_crow_rk.h).
 __device__ __forceinline__ void vec_stages(const double (&skl)[12], const double (&skr)[12],
-                                           double h, double dq, double dp, double (&kq)[12][1],
+                                           dop853::Coef cf, double h, double dq, double dp, double (&kq)[12][1],
                                            double (&kp)[12][1]) {
   using namespace fputrow;
   dop853::static_for<0, 12>([&](auto ic) {
     constexpr int I = decltype(ic)::value;
-    const double Yq = dq + dop853::stage_sum<I>(kq, 0);
-    const double Yp = dp + dop853::stage_sum<I>(kp, 0);
+    const double Yq = dq + dop853::stage_sum<I>(cf, kq, 0);
+    const double Yp = dp + dop853::stage_sum<I>(cf, kp, 0);
     const double ql = dpp<0x111>(Yq);  // row_shr:1
     const double qr = dpp<0x101>(Yq);  // row_shl:1
     double hq = (skl[I] + skr[I]) * Yq;
@@ -140,18 +140,20 @@ struct CRowRKL : CRowRK<N, 0> {
   // one fixed DOP853 step of size h
   __device__ void rk_step(const StepArgs &a, double h, bool do_ld) {
     {
+      const dop853::Coef cf = dop853::coef();
       double kq[12][1], kp[12][1], g = 0.0;
-      B::state_pass(a, h, do_ld, kq, kp, g);
-      q += dop853::final_sum(kq, 0);
-      p += dop853::final_sum(kp, 0);
+      B::state_pass(a, cf, h, do_ld, kq, kp, g);
+      q += dop853::final_sum(cf, kq, 0);
+      p += dop853::final_sum(cf, kp, 0);
       if (do_ld) ld = __builtin_fma(h, fputrow::row_sum(g), ld);
     }
     for (int v = 0; v < M; ++v) {
+      const dop853::Coef cf = dop853::coef();
       double kq[12][1], kp[12][1];
       const double dq = cq(vec, v), dp = cp(vec, v);
-      rkl::vec_stages(skl, skr, h, dq, dp, kq, kp);
-      cq(vec, v) = dq + dop853::final_sum(kq, 0);
-      cp(vec, v) = dp + dop853::final_sum(kp, 0);
+      rkl::vec_stages(skl, skr, cf, h, dq, dp, kq, kp);
+      cq(vec, v) = dq + dop853::final_sum(cf, kq, 0);
+      cp(vec, v) = dp + dop853::final_sum(cf, kp, 0);
     }
   }
 
@@ -163,26 +165,28 @@ struct CRowRKL : CRowRK<N, 0> {
                                double &ldn) {
     double e5 = 0.0, e3 = 0.0;
     {
+      const dop853::Coef cf = dop853::coef();
       double kq[12][1], kp[12][1], g = 0.0;
-      B::state_pass(a, h, do_ld, kq, kp, g);
-      const double sq = dop853::final_sum(kq, 0), sp = dop853::final_sum(kp, 0);
+      B::state_pass(a, cf, h, do_ld, kq, kp, g);
+      const double sq = dop853::final_sum(cf, kq, 0), sp = dop853::final_sum(cf, kp, 0);
       qn = q + sq;
       pn = p + sp;
       if (mass) {
-        dop853::err_terms(kq, 0, q, qn, sq, a.rtol, a.atol, e5, e3);
-        dop853::err_terms(kp, 0, p, pn, sp, a.rtol, a.atol, e5, e3);
+        dop853::err_terms(cf, kq, 0, q, qn, sq, a.rtol, a.atol, e5, e3);
+        dop853::err_terms(cf, kp, 0, p, pn, sp, a.rtol, a.atol, e5, e3);
       }
       ldn = do_ld ? __builtin_fma(h, fputrow::row_sum(g), ld) : ld;
     }
     for (int v = 0; v < M; ++v) {
+      const dop853::Coef cf = dop853::coef();
       double kq[12][1], kp[12][1];
       const double dq = cq(vec, v), dp = cp(vec, v);
-      rkl::vec_stages(skl, skr, h, dq, dp, kq, kp);
-      const double sq = dop853::final_sum(kq, 0), sp = dop853::final_sum(kp, 0);
+      rkl::vec_stages(skl, skr, cf, h, dq, dp, kq, kp);
+      const double sq = dop853::final_sum(cf, kq, 0), sp = dop853::final_sum(cf, kp, 0);
       const double dqn = dq + sq, dpn = dp + sp;
       if (mass) {
-        dop853::err_terms(kq, 0, dq, dqn, sq, a.rtol, a.atol, e5, e3);
-        dop853::err_terms(kp, 0, dp, dpn, sp, a.rtol, a.atol, e5, e3);
+        dop853::err_terms(cf, kq, 0, dq, dqn, sq, a.rtol, a.atol, e5, e3);
+        dop853::err_terms(cf, kp, 0, dp, dpn, sp, a.rtol, a.atol, e5, e3);
       }
       cq(vnew, v) = dqn;
       cp(vnew, v) = dpn;

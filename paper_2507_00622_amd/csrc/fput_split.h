@@ -83,16 +83,16 @@ struct CRowSplit : CRowRK<N, 1> {
   }
 
   // the 12 stages of the state and of this row's vector, stage by stage
-  __device__ __forceinline__ void stages(const StepArgs &a, double h, bool do_ld,
+  __device__ __forceinline__ void stages(const StepArgs &a, dop853::Coef cf, double h, bool do_ld,
                                          double (&kq)[12][1], double (&kp)[12][1],
                                          double (&vq)[12][1], double (&vp)[12][1], double &g) {
     using namespace fputrow;
     dop853::static_for<0, 12>([&](auto ic) {
       constexpr int I = decltype(ic)::value;
-      const double Yq = q + dop853::stage_sum<I>(kq, 0);
-      const double Yp = p + dop853::stage_sum<I>(kp, 0);
-      const double Vq = dq[0] + dop853::stage_sum<I>(vq, 0);
-      const double Vp = dp[0] + dop853::stage_sum<I>(vp, 0);
+      const double Yq = q + dop853::stage_sum<I>(cf, kq, 0);
+      const double Yp = p + dop853::stage_sum<I>(cf, kp, 0);
+      const double Vq = dq[0] + dop853::stage_sum<I>(cf, vq, 0);
+      const double Vp = dp[0] + dop853::stage_sum<I>(cf, vp, 0);
       double F, kl, kr;
       O::spring_terms(a, Yq, mass, F, kl, kr);
       if constexpr (dop853::B[I] != 0.0) {
@@ -111,23 +111,24 @@ struct CRowSplit : CRowRK<N, 1> {
   }
 
   __device__ __forceinline__ void rk_step(const StepArgs &a, double h, bool do_ld) {
+    const dop853::Coef cf = dop853::coef();
     double kq[12][1], kp[12][1], vq[12][1], vp[12][1], g = 0.0;
-    stages(a, h, do_ld, kq, kp, vq, vp, g);
-    q += dop853::final_sum(kq, 0);
-    p += dop853::final_sum(kp, 0);
+    stages(a, cf, h, do_ld, kq, kp, vq, vp, g);
+    q += dop853::final_sum(cf, kq, 0);
+    p += dop853::final_sum(cf, kp, 0);
     if (do_ld) ld = __builtin_fma(h, fputrow::row_sum(g), ld);
-    dq[0] += dop853::final_sum(vq, 0);
-    dp[0] += dop853::final_sum(vp, 0);
+    dq[0] += dop853::final_sum(cf, vq, 0);
+    dp[0] += dop853::final_sum(cf, vp, 0);
   }
 
   // The scaled error terms of one component (dop853::err_terms before the
   // squares).
-  __device__ __forceinline__ static void ratios(const StepArgs &a, const double (&k)[12][1],
+  __device__ __forceinline__ static void ratios(const StepArgs &a, dop853::Coef cf, const double (&k)[12][1],
                                                 double y, double yn, double sb, double &r5,
                                                 double &r3) {
     const double sk = __builtin_fma(
         a.rtol, __builtin_fmax(__builtin_fabs(y), __builtin_fabs(yn)), a.atol);
-    r5 = dop853::err5_sum(k, 0) / sk;
+    r5 = dop853::err5_sum(cf, k, 0) / sk;
     r3 = (sb - dop853::BHH1 * k[0][0] - dop853::BHH2 * k[8][0] - dop853::BHH3 * k[11][0]) / sk;
   }
 
@@ -136,20 +137,21 @@ struct CRowSplit : CRowRK<N, 1> {
   __device__ __forceinline__ double rk_attempt(const StepArgs &a, double h, bool do_ld,
                                                double (*ex)[64], double &qn, double &pn,
                                                double &dqn, double &dpn, double &ldn) {
+    const dop853::Coef cf = dop853::coef();
     double kq[12][1], kp[12][1], vq[12][1], vp[12][1], g = 0.0;
-    stages(a, h, do_ld, kq, kp, vq, vp, g);
-    const double sq = dop853::final_sum(kq, 0), sp = dop853::final_sum(kp, 0);
+    stages(a, cf, h, do_ld, kq, kp, vq, vp, g);
+    const double sq = dop853::final_sum(cf, kq, 0), sp = dop853::final_sum(cf, kp, 0);
     qn = q + sq;
     pn = p + sp;
-    const double tq = dop853::final_sum(vq, 0), tp = dop853::final_sum(vp, 0);
+    const double tq = dop853::final_sum(cf, vq, 0), tp = dop853::final_sum(cf, vp, 0);
     dqn = dq[0] + tq;
     dpn = dp[0] + tp;
     ldn = do_ld ? __builtin_fma(h, fputrow::row_sum(g), ld) : ld;
     double s5q, s3q, s5p, s3p, v5q, v3q, v5p, v3p;
-    ratios(a, kq, q, qn, sq, s5q, s3q);
-    ratios(a, kp, p, pn, sp, s5p, s3p);
-    ratios(a, vq, dq[0], dqn, tq, v5q, v3q);
-    ratios(a, vp, dp[0], dpn, tp, v5p, v3p);
+    ratios(a, cf, kq, q, qn, sq, s5q, s3q);
+    ratios(a, cf, kp, p, pn, sp, s5p, s3p);
+    ratios(a, cf, vq, dq[0], dqn, tq, v5q, v3q);
+    ratios(a, cf, vp, dp[0], dpn, tp, v5p, v3p);
     // one wavefront, whose LDS accesses execute in program order
     const int tid = threadIdx.x;
     wave_sync();

@@ -26,12 +26,12 @@ namespace quad {
 // one component's contributions to dop853::err_terms, before they are squared
 // and summed
 template <int D2>
-__device__ __forceinline__ void err_ratios(const double (&k)[12][D2], int c, double y, double yn,
+__device__ __forceinline__ void err_ratios(dop853::Coef cf, const double (&k)[12][D2], int c, double y, double yn,
                                            double sb, double rtol, double atol, double &r5,
                                            double &r3) {
   const double sk = __builtin_fma(rtol, __builtin_fmax(__builtin_fabs(y), __builtin_fabs(yn)),
                                   atol);
-  r5 = dop853::err5_sum(k, c) / sk;
+  r5 = dop853::err5_sum(cf, k, c) / sk;
   r3 = (sb - dop853::BHH1 * k[0][c] - dop853::BHH2 * k[8][c] - dop853::BHH3 * k[11][c]) / sk;
 }
 
@@ -105,12 +105,12 @@ struct QuadRK {
   // derivative at Y = y + sum_j a_Ij k_j; the LD integrand of the state
   // into g (lane 0's is the orbit's).
   template <int I>
-  __device__ __forceinline__ void stage(const StepArgs &a, double h, bool do_ld,
+  __device__ __forceinline__ void stage(const StepArgs &a, dop853::Coef cf, double h, bool do_ld,
                                         double (&k)[12][D], double &g) {
     using namespace quad;
     double Y[D];
 #pragma unroll
-    for (int c = 0; c < D; ++c) Y[c] = y[c] + dop853::stage_sum<I>(k, c);
+    for (int c = 0; c < D; ++c) Y[c] = y[c] + dop853::stage_sum<I>(cf, k, c);
     double f[D];  // lane 0: f(Y)
     if constexpr (GEN) {
       double X[D], dY[1][D], df[1][D];
@@ -160,11 +160,12 @@ struct QuadRK {
 
   // one fixed step of size h
   __device__ __forceinline__ void rk_step(const StepArgs &a, double h, bool do_ld) {
+    const dop853::Coef cf = dop853::coef();
     double k[12][D], g = 0.0;
     dop853::static_for<0, 12>(
-        [&](auto ic) { stage<decltype(ic)::value>(a, h, do_ld, k, g); });
+        [&](auto ic) { stage<decltype(ic)::value>(a, cf, h, do_ld, k, g); });
 #pragma unroll
-    for (int c = 0; c < D; ++c) y[c] += dop853::final_sum(k, c);
+    for (int c = 0; c < D; ++c) y[c] += dop853::final_sum(cf, k, c);
     if (do_ld) ld = __builtin_fma(h, quad::from<0>(g), ld);
   }
 
@@ -173,16 +174,17 @@ struct QuadRK {
   __device__ __forceinline__ double rk_attempt(const StepArgs &a, double h, bool do_ld,
                                                double (&yn)[D], double &ldn) {
     using namespace quad;
+    const dop853::Coef cf = dop853::coef();
     double k[12][D], g = 0.0;
     dop853::static_for<0, 12>(
-        [&](auto ic) { stage<decltype(ic)::value>(a, h, do_ld, k, g); });
+        [&](auto ic) { stage<decltype(ic)::value>(a, cf, h, do_ld, k, g); });
     ldn = do_ld ? __builtin_fma(h, from<0>(g), ld) : ld;
     double r5[D], r3[D];
 #pragma unroll
     for (int c = 0; c < D; ++c) {
-      const double sb = dop853::final_sum(k, c);
+      const double sb = dop853::final_sum(cf, k, c);
       yn[c] = y[c] + sb;
-      err_ratios(k, c, y[c], yn[c], sb, a.rtol, a.atol, r5[c], r3[c]);
+      err_ratios(cf, k, c, y[c], yn[c], sb, a.rtol, a.atol, r5[c], r3[c]);
     }
     // the sums run over the state's components, then each vector's: every
     // lane adds its own to what the lane before handed on

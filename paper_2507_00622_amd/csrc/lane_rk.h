@@ -38,16 +38,29 @@ namespace chx {
 
 
 
-// LDS doubles per stage record: a general system's record, else the positions
-template <class S, bool GEN>
+// Fixed-step Henon-Heiles with three or more vectors records each stage's
+// step-scaled Hessian (3 doubles) instead of its position (2), so the vector
+// passes read it instead of forming it anew: 36 of about 400 instructions per
+// vector and step, for 288 instead of 192 bytes of LDS per orbit, which the two
+// wavefronts per SIMD that the registers allow still leave room for (147 of
+// 160 KB).  With three degrees of freedom the Hessian is six doubles to
+// three and would halve the wavefronts.
+template <class S, int M>
+constexpr bool hess_record = false;
+template <int M>
+constexpr bool hess_record<SysHH, M> = M >= 3;
+
+// LDS doubles per stage record: a general system's record, the Hessian, or
+// the positions
+template <class S, bool GEN, bool HR>
 constexpr int rec_width() {
   if constexpr (GEN)
     return S::NREC;
   else
-    return S::N;
+    return HR ? S::NH : S::N;
 }
 
-template <class S, int M, bool GP>
+template <class S, int M, bool GP, bool HR = false>
 struct RKOrbit : LaneOrbit<S, M, GP, -1> {
   using Base = LaneOrbit<S, M, GP, -1>;
   using Base::N;
@@ -60,7 +73,7 @@ struct RKOrbit : LaneOrbit<S, M, GP, -1> {
   // (dual numbers); its stages keep the records in LDS, a separable one's
   // the positions.
   static constexpr bool GEN = has_hamiltonian<S>::value;
-  static constexpr int QW = rec_width<S, GEN>();  // LDS doubles per stage and thread
+  static constexpr int QW = rec_width<S, GEN, HR>();  // LDS doubles per stage and thread
   // With one or two vectors a general system integrates the state and the
   // vectors stage by stage in one pass: one evaluation on multi-dual
   // numbers gives the field and every vector's derivative (the values
@@ -74,16 +87,16 @@ struct RKOrbit : LaneOrbit<S, M, GP, -1> {
   // sum_j a_Ij k_j, dY_v = w_v + sum_j a_Ij kv_vj; k_I = h f(Y),
   // kv_vI = h Df(Y) dY_v; the LD integrand at weighted stages into g.
   template <int I>
-  __device__ __forceinline__ void fused_stage(const StepArgs &a, double h, bool do_ld,
+  __device__ __forceinline__ void fused_stage(const StepArgs &a, dop853::Coef cf, double h, bool do_ld,
                                               double (&k)[12][D], double (&kv)[M][12][D],
                                               double &g) {
     double Y[D], dY[M][D], f[D], df[M][D];
 #pragma unroll
-    for (int c = 0; c < D; ++c) Y[c] = x[c] + dop853::stage_sum<I>(k, c);
+    for (int c = 0; c < D; ++c) Y[c] = x[c] + dop853::stage_sum<I>(cf, k, c);
 #pragma unroll
     for (int v = 0; v < M; ++v)
 #pragma unroll
-      for (int c = 0; c < D; ++c) dY[v][c] = w[v][c] + dop853::stage_sum<I>(kv[v], c);
+      for (int c = 0; c < D; ++c) dY[v][c] = w[v][c] + dop853::stage_sum<I>(cf, kv[v], c);
     S::template rhs_multi<M>(Y, dY, f, df, a.prm);
     if constexpr (dop853::B[I] != 0.0) {
       if (do_ld) {
@@ -115,12 +128,12 @@ struct RKOrbit : LaneOrbit<S, M, GP, -1> {
   // Stage I of the state: Y = x + sum_j a_Ij k_j; its LDS record; the LD
   // integrand sum |dY/dt|^p at weighted stages into g; k_I = h f(Y).
   template <int I>
-  __device__ __forceinline__ void state_stage(const StepArgs &a, double h, bool do_ld,
+  __device__ __forceinline__ void state_stage(const StepArgs &a, dop853::Coef cf, double h, bool do_ld,
                                               double *qs, int stride, double (&k)[12][D],
                                               double &g) {
     double Y[D], f[D];
 #pragma unroll
-    for (int c = 0; c < D; ++c) Y[c] = x[c] + dop853::stage_sum<I>(k, c);
+    for (int c = 0; c < D; ++c) Y[c] = x[c] + dop853::stage_sum<I>(cf, k, c);
     if constexpr (GEN) {
       double rec[QW];
       S::rhs_rec(Y, f, rec, a.prm);
@@ -129,7 +142,12 @@ struct RKOrbit : LaneOrbit<S, M, GP, -1> {
         for (int r = 0; r < QW; ++r) qs[(I * QW + r) * stride] = rec[r];
       }
     } else {
-      if constexpr (M > 0) {
+      if constexpr (HR) {
+        double Hs[S::NH];
+        S::hess_scaled(Y, h, Hs, a.prm);
+#pragma unroll
+        for (int r = 0; r < QW; ++r) qs[(I * QW + r) * stride] = Hs[r];
+      } else if constexpr (M > 0) {
 #pragma unroll
         for (int r = 0; r < QW; ++r) qs[(I * QW + r) * stride] = Y[r];
       }
@@ -161,12 +179,12 @@ struct RKOrbit : LaneOrbit<S, M, GP, -1> {
   // Stage I of a deviation vector starting at w0: dY = w0 + sum_j a_Ij k_j,
   // k_I = h Df(Y_I) dY with Y_I the state's stage (from LDS).
   template <int I>
-  __device__ __forceinline__ void vector_stage(const StepArgs &a, double h, const double *w0,
+  __device__ __forceinline__ void vector_stage(const StepArgs &a, dop853::Coef cf, double h, const double *w0,
                                                const double *qs, int stride,
                                                double (&k)[12][D]) {
     double Y[D];
 #pragma unroll
-    for (int c = 0; c < D; ++c) Y[c] = w0[c] + dop853::stage_sum<I>(k, c);
+    for (int c = 0; c < D; ++c) Y[c] = w0[c] + dop853::stage_sum<I>(cf, k, c);
     if constexpr (GEN) {
       // the records do not depend on the vector: with a plain LDS offset the
       // optimiser loads each stage's record once for all vectors and keeps
@@ -181,10 +199,16 @@ struct RKOrbit : LaneOrbit<S, M, GP, -1> {
 #pragma unroll
       for (int c = 0; c < D; ++c) k[I][c] = h * f[c];
     } else {
-      double Hs[S::NH], q[N];
+      double Hs[S::NH];
+      if constexpr (HR) {
 #pragma unroll
-      for (int r = 0; r < N; ++r) q[r] = qs[(I * N + r) * stride];
-      S::hess_scaled(q, h, Hs, a.prm);
+        for (int r = 0; r < QW; ++r) Hs[r] = qs[(I * QW + r) * stride];
+      } else {
+        double q[N];
+#pragma unroll
+        for (int r = 0; r < N; ++r) q[r] = qs[(I * N + r) * stride];
+        S::hess_scaled(q, h, Hs, a.prm);
+      }
 #pragma unroll
       for (int r = 0; r < N; ++r) {
         double s = 0.0;
@@ -203,38 +227,41 @@ struct RKOrbit : LaneOrbit<S, M, GP, -1> {
     if constexpr (FUSED) {
       double k[12][D], kv[M][12][D];
       double g = 0.0;
+      const dop853::Coef cf = dop853::coef();
       dop853::static_for<0, 12>([&](auto ic) {
-        fused_stage<decltype(ic)::value>(a, h, do_ld, k, kv, g);
+        fused_stage<decltype(ic)::value>(a, cf, h, do_ld, k, kv, g);
       });
 #pragma unroll
-      for (int c = 0; c < D; ++c) x[c] += dop853::final_sum(k, c);
+      for (int c = 0; c < D; ++c) x[c] += dop853::final_sum(cf, k, c);
 #pragma unroll
       for (int v = 0; v < M; ++v)
 #pragma unroll
-        for (int c = 0; c < D; ++c) w[v][c] += dop853::final_sum(kv[v], c);
+        for (int c = 0; c < D; ++c) w[v][c] += dop853::final_sum(cf, kv[v], c);
       if (do_ld) ld = __builtin_fma(h, g, ld);
       return;
     }
     {
+      const dop853::Coef cf = dop853::coef();
       double k[12][D];  // h f(Y_i) of the state
       double g = 0.0;   // sum_i b_i (LD integrand at stage i)
       dop853::static_for<0, 12>([&](auto ic) {
-        state_stage<decltype(ic)::value>(a, h, do_ld, qs, stride, k, g);
+        state_stage<decltype(ic)::value>(a, cf, h, do_ld, qs, stride, k, g);
       });
 #pragma unroll
-      for (int c = 0; c < D; ++c) x[c] += dop853::final_sum(k, c);
+      for (int c = 0; c < D; ++c) x[c] += dop853::final_sum(cf, k, c);
       if (do_ld) ld = __builtin_fma(h, g, ld);
     }
     __builtin_amdgcn_sched_barrier(0);
     // (a compile-time loop: the vectors must stay in registers)
     dop853::static_for<0, M>([&](auto vc) {
       constexpr int v = decltype(vc)::value;
+      const dop853::Coef cf = dop853::coef();
       double k[12][D];  // h f(dY_i) of vector v
       dop853::static_for<0, 12>([&](auto ic) {
-        vector_stage<decltype(ic)::value>(a, h, w[v], qs, stride, k);
+        vector_stage<decltype(ic)::value>(a, cf, h, w[v], qs, stride, k);
       });
 #pragma unroll
-      for (int c = 0; c < D; ++c) w[v][c] += dop853::final_sum(k, c);
+      for (int c = 0; c < D; ++c) w[v][c] += dop853::final_sum(cf, k, c);
       // one vector pass at a time: overlapped by the scheduler, two passes'
       // stage derivatives would be live together
       __builtin_amdgcn_sched_barrier(0);
@@ -255,53 +282,56 @@ struct RKOrbit : LaneOrbit<S, M, GP, -1> {
     if constexpr (FUSED) {
       double k[12][D], kv[M][12][D];
       double g = 0.0;
+      const dop853::Coef cf = dop853::coef();
       dop853::static_for<0, 12>([&](auto ic) {
-        fused_stage<decltype(ic)::value>(a, h, do_ld, k, kv, g);
+        fused_stage<decltype(ic)::value>(a, cf, h, do_ld, k, kv, g);
       });
 #pragma unroll
       for (int c = 0; c < D; ++c) {
-        const double sb = dop853::final_sum(k, c);
+        const double sb = dop853::final_sum(cf, k, c);
         xn[c] = x[c] + sb;
-        dop853::err_terms(k, c, x[c], xn[c], sb, a.rtol, a.atol, e5, e3);
+        dop853::err_terms(cf, k, c, x[c], xn[c], sb, a.rtol, a.atol, e5, e3);
       }
       ldn = do_ld ? __builtin_fma(h, g, ld) : ld;
 #pragma unroll
       for (int v = 0; v < M; ++v)
 #pragma unroll
         for (int c = 0; c < D; ++c) {
-          const double sb = dop853::final_sum(kv[v], c);
+          const double sb = dop853::final_sum(cf, kv[v], c);
           const double yn = w[v][c] + sb;
           wn[(v * D + c) * stride] = yn;
-          dop853::err_terms(kv[v], c, w[v][c], yn, sb, a.rtol, a.atol, e5, e3);
+          dop853::err_terms(cf, kv[v], c, w[v][c], yn, sb, a.rtol, a.atol, e5, e3);
         }
     } else {
       {
+        const dop853::Coef cf = dop853::coef();
         double k[12][D];
         double g = 0.0;
         dop853::static_for<0, 12>([&](auto ic) {
-          state_stage<decltype(ic)::value>(a, h, do_ld, qs, stride, k, g);
+          state_stage<decltype(ic)::value>(a, cf, h, do_ld, qs, stride, k, g);
         });
 #pragma unroll
         for (int c = 0; c < D; ++c) {
-          const double sb = dop853::final_sum(k, c);
+          const double sb = dop853::final_sum(cf, k, c);
           xn[c] = x[c] + sb;
-          dop853::err_terms(k, c, x[c], xn[c], sb, a.rtol, a.atol, e5, e3);
+          dop853::err_terms(cf, k, c, x[c], xn[c], sb, a.rtol, a.atol, e5, e3);
         }
         ldn = do_ld ? __builtin_fma(h, g, ld) : ld;
       }
       __builtin_amdgcn_sched_barrier(0);
       dop853::static_for<0, M>([&](auto vc) {
         constexpr int v = decltype(vc)::value;
+        const dop853::Coef cf = dop853::coef();
         double k[12][D];
         dop853::static_for<0, 12>([&](auto ic) {
-          vector_stage<decltype(ic)::value>(a, h, w[v], qs, stride, k);
+          vector_stage<decltype(ic)::value>(a, cf, h, w[v], qs, stride, k);
         });
 #pragma unroll
         for (int c = 0; c < D; ++c) {
-          const double sb = dop853::final_sum(k, c);
+          const double sb = dop853::final_sum(cf, k, c);
           const double yn = w[v][c] + sb;
           wn[(v * D + c) * stride] = yn;
-          dop853::err_terms(k, c, w[v][c], yn, sb, a.rtol, a.atol, e5, e3);
+          dop853::err_terms(cf, k, c, w[v][c], yn, sb, a.rtol, a.atol, e5, e3);
         }
         __builtin_amdgcn_sched_barrier(0);
       });
@@ -321,7 +351,7 @@ __global__ void __launch_bounds__(256) lane_rk_kernel(const StepArgs a) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= a.n) return;
   if (a.st[i] != CHX_ORBIT_OK) return;
-  RKOrbit<S, M, GP> o;
+  RKOrbit<S, M, GP, hess_record<S, M>> o;
   o.load(a, i);
   const bool do_ld = (a.ind & CHX_IND_LD) != 0;
   const double h = a.dt;
@@ -463,7 +493,7 @@ struct LaneRKDispatch {
       // LDS per thread: stage records, and for the adaptive solver the
       // attempted vectors; at most 64 KB per block (smaller blocks where
       // needed)
-      constexpr int QW = RKOrbit<S, M, false>::LDS_STAGE;
+      constexpr int QW = RKOrbit<S, M, false, !ADAPT && hess_record<S, M>>::LDS_STAGE;
       const size_t per = M > 0 ? sizeof(double) * (12 * QW + (adaptive ? M * 2 * S::N : 0)) : 0;
       while (block > 64 && per * (size_t)block > 65536) block /= 2;
       const int64_t grid = (a.n + block - 1) / block;
