@@ -50,6 +50,16 @@ constexpr bool hess_record = false;
 template <int M>
 constexpr bool hess_record<SysHH, M> = M >= 3;
 
+// With five or more vectors its registers allow two wavefronts per SIMD at
+// best, and the vectors go through the stages two at a time: the coefficients
+// and Hessians are read once for both, and eight sums instead of four hide each
+// other's latency (held to 256 VGPRs, what spills is outside the step
+// loop).  212,700 orbits, six vectors, 1,000 steps: 31.5 ms with literal
+// coefficients and one vector a pass, 27.4 with the coefficients in
+// constant memory and the Hessian record, 26.3 with the pairs.
+template <class S, int M>
+constexpr bool pair_passes = hess_record<S, M> && M >= 5;
+
 // LDS doubles per stage record: a general system's record, the Hessian, or
 // the positions
 template <class S, bool GEN, bool HR>
@@ -252,8 +262,24 @@ struct RKOrbit : LaneOrbit<S, M, GP, -1> {
       if (do_ld) ld = __builtin_fma(h, g, ld);
     }
     __builtin_amdgcn_sched_barrier(0);
-    // (a compile-time loop: the vectors must stay in registers)
-    dop853::static_for<0, M>([&](auto vc) {
+    // (compile-time loops: the vectors must stay in registers)
+    constexpr int MP = HR && pair_passes<S, M> ? M & ~1 : 0;  // vectors taken two at a time
+    dop853::static_for<0, MP / 2>([&](auto pc) {
+      constexpr int v = 2 * decltype(pc)::value;
+      const dop853::Coef cf = dop853::coef();
+      double k[12][D], l[12][D];
+      dop853::static_for<0, 12>([&](auto ic) {
+        vector_stage<decltype(ic)::value>(a, cf, h, w[v], qs, stride, k);
+        vector_stage<decltype(ic)::value>(a, cf, h, w[v + 1], qs, stride, l);
+      });
+#pragma unroll
+      for (int c = 0; c < D; ++c) {
+        w[v][c] += dop853::final_sum(cf, k, c);
+        w[v + 1][c] += dop853::final_sum(cf, l, c);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    dop853::static_for<MP, M>([&](auto vc) {
       constexpr int v = decltype(vc)::value;
       const dop853::Coef cf = dop853::coef();
       double k[12][D];  // h f(dY_i) of vector v
@@ -347,7 +373,8 @@ struct RKOrbit : LaneOrbit<S, M, GP, -1> {
 extern __shared__ double lane_rk_lds[];
 
 template <class S, int M, bool GP>
-__global__ void __launch_bounds__(256) lane_rk_kernel(const StepArgs a) {
+__global__ void __launch_bounds__(256, (pair_passes<S, M> ? 2 : 1))
+    lane_rk_kernel(const StepArgs a) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= a.n) return;
   if (a.st[i] != CHX_ORBIT_OK) return;
