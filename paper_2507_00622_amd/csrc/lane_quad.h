@@ -45,6 +45,65 @@ __device__ __forceinline__ double from(double v) {
   return qp<L * 0x55>(v);
 }
 
+// Stage I of an orbit's objects, one per lane: k_I = h times the object's
+// derivative at Y = y + sum_j a_Ij k_j, where the state's lane gives the state's
+// stage to the others (from_state); the LD integrand of the state into
+// g (the state's lane has the orbit's).
+template <class S, int I, int D, class F>
+__device__ __forceinline__ void stage(const StepArgs &a, dop853::Coef cf, double h, bool do_ld,
+                                      const double (&y)[D], bool state, double (&k)[12][D],
+                                      double &g, F &&from_state) {
+  constexpr int N = S::N;
+  double Y[D];
+#pragma unroll
+  for (int c = 0; c < D; ++c) Y[c] = y[c] + dop853::stage_sum<I>(cf, k, c);
+  double f[D];  // the state's lane: f(Y)
+  if constexpr (has_hamiltonian<S>::value) {
+    double X[D], dY[1][D], df[1][D];
+#pragma unroll
+    for (int c = 0; c < D; ++c) {
+      X[c] = from_state(Y[c]);
+      dY[0][c] = Y[c];
+    }
+    S::template rhs_multi<1>(X, dY, f, df, a.prm);
+#pragma unroll
+    for (int c = 0; c < D; ++c) k[I][c] = h * (state ? f[c] : df[0][c]);
+  } else {
+    double q[N], F_[N], Hs[S::NH];
+#pragma unroll
+    for (int r = 0; r < N; ++r) q[r] = from_state(Y[r]);
+    S::force(q, F_, a.prm);
+    S::hess_scaled(q, h, Hs, a.prm);
+#pragma unroll
+    for (int r = 0; r < N; ++r) {
+      double s = 0.0;
+#pragma unroll
+      for (int j = 0; j < N; ++j) s = __builtin_fma(Hs[hidx(N, r, j)], Y[j], s);
+      f[r] = Y[N + r];
+      f[N + r] = -F_[r];
+      k[I][r] = h * Y[N + r];
+      k[I][N + r] = state ? h * f[N + r] : -s;
+    }
+  }
+  if constexpr (dop853::B[I] != 0.0) {
+    if (do_ld) {
+      double gi = 0.0;
+      if constexpr (has_hamiltonian<S>::value) {
+#pragma unroll
+        for (int c = 0; c < D; ++c) gi += sqrt_ld(f[c]);
+      } else {
+#pragma unroll
+        for (int r = 0; r < N; ++r) gi += sqrt_ld(f[r]) + sqrt_ld(f[N + r]);
+      }
+      g = __builtin_fma(dop853::B[I], gi, g);
+    }
+  }
+  // each stage finishes before the next: run ahead, the value chain of
+  // all twelve would keep every stage's intermediates live
+#pragma unroll
+  for (int c = 0; c < D; ++c) asm volatile("" : "+v"(k[I][c]));
+}
+
 }  // namespace quad
 
 template <class S>
@@ -101,69 +160,12 @@ struct QuadRK {
     }
   }
 
-  // Stage I of the quad's three objects: k_I = h times the object's
-  // derivative at Y = y + sum_j a_Ij k_j; the LD integrand of the state
-  // into g (lane 0's is the orbit's).
-  template <int I>
-  __device__ __forceinline__ void stage(const StepArgs &a, dop853::Coef cf, double h, bool do_ld,
-                                        double (&k)[12][D], double &g) {
-    using namespace quad;
-    double Y[D];
-#pragma unroll
-    for (int c = 0; c < D; ++c) Y[c] = y[c] + dop853::stage_sum<I>(cf, k, c);
-    double f[D];  // lane 0: f(Y)
-    if constexpr (GEN) {
-      double X[D], dY[1][D], df[1][D];
-#pragma unroll
-      for (int c = 0; c < D; ++c) {
-        X[c] = from<0>(Y[c]);
-        dY[0][c] = Y[c];
-      }
-      S::template rhs_multi<1>(X, dY, f, df, a.prm);
-#pragma unroll
-      for (int c = 0; c < D; ++c) k[I][c] = h * (state ? f[c] : df[0][c]);
-    } else {
-      double q[N], F[N], Hs[S::NH];
-#pragma unroll
-      for (int r = 0; r < N; ++r) q[r] = from<0>(Y[r]);
-      S::force(q, F, a.prm);
-      S::hess_scaled(q, h, Hs, a.prm);
-#pragma unroll
-      for (int r = 0; r < N; ++r) {
-        double s = 0.0;
-#pragma unroll
-        for (int j = 0; j < N; ++j) s = __builtin_fma(Hs[hidx(N, r, j)], Y[j], s);
-        f[r] = Y[N + r];
-        f[N + r] = -F[r];
-        k[I][r] = h * Y[N + r];
-        k[I][N + r] = state ? h * f[N + r] : -s;
-      }
-    }
-    if constexpr (dop853::B[I] != 0.0) {
-      if (do_ld) {
-        double gi = 0.0;
-        if constexpr (GEN) {
-#pragma unroll
-          for (int c = 0; c < D; ++c) gi += sqrt_ld(f[c]);
-        } else {
-#pragma unroll
-          for (int r = 0; r < N; ++r) gi += sqrt_ld(f[r]) + sqrt_ld(f[N + r]);
-        }
-        g = __builtin_fma(dop853::B[I], gi, g);
-      }
-    }
-    // each stage finishes before the next: run ahead, the value chain of
-    // all twelve would keep every stage's intermediates live
-#pragma unroll
-    for (int c = 0; c < D; ++c) asm volatile("" : "+v"(k[I][c]));
-  }
-
   // one fixed step of size h
   __device__ __forceinline__ void rk_step(const StepArgs &a, double h, bool do_ld) {
     const dop853::Coef cf = dop853::coef();
     double k[12][D], g = 0.0;
     dop853::static_for<0, 12>(
-        [&](auto ic) { stage<decltype(ic)::value>(a, cf, h, do_ld, k, g); });
+        [&](auto ic) { quad::stage<S, decltype(ic)::value>(a, cf, h, do_ld, y, state, k, g, quad::from<0>); });
 #pragma unroll
     for (int c = 0; c < D; ++c) y[c] += dop853::final_sum(cf, k, c);
     if (do_ld) ld = __builtin_fma(h, quad::from<0>(g), ld);
@@ -177,7 +179,7 @@ struct QuadRK {
     const dop853::Coef cf = dop853::coef();
     double k[12][D], g = 0.0;
     dop853::static_for<0, 12>(
-        [&](auto ic) { stage<decltype(ic)::value>(a, cf, h, do_ld, k, g); });
+        [&](auto ic) { quad::stage<S, decltype(ic)::value>(a, cf, h, do_ld, y, state, k, g, quad::from<0>); });
     ldn = do_ld ? __builtin_fma(h, from<0>(g), ld) : ld;
     double r5[D], r3[D];
 #pragma unroll

@@ -1,8 +1,8 @@
 """Small ensembles against large ones, bit for bit.
 
-Small ensembles of a SALI pair (lane systems, DOP853) or of two to four
-SALI/GALI vectors (FPU chains) run on several lanes or rows per orbit; the
-same orbits inside an ensemble beyond the kernels' size limit run on one.
+Small ensembles of the lane systems (a SALI pair, or three and more vectors)
+or of two to four SALI/GALI vectors (FPU chains) run on several lanes or rows
+per orbit; the same orbits inside an ensemble beyond the kernels' size limit run on one.
 Both take the same operations in the same order, so every output agrees in
 every bit: regular and chaotic orbits, masked, non-finite, escaping and
 early-exiting ones, checkpoint periods that do not divide the run.
@@ -106,3 +106,29 @@ def test_row_per_vector(env, N, m, integ):
         if ind & O.IND_SALI:
             kw.update(early_exit=True, sali_threshold=0.3)
         compare(env, P.fput(N), x0, 2100, m, **kw)
+
+
+@pytest.mark.parametrize("integ", ["yoshida4", "dop853"])
+@pytest.mark.parametrize("name,m", [("hh", 3), ("hh", 4), ("quartic1", 2), ("quartic2", 3),
+                                    ("quartic3", 6), ("harmonic2", 4), ("dp", 4)])
+def test_lane_per_vector(env, name, m, integ):
+    torch, P, O = env
+    if name == "dp" and integ == "yoshida4":
+        pytest.skip("no Yoshida-4 for the double pendulum")
+    n = 77  # the last wavefront holds one orbit of four
+    print(f"case: a lane per vector {name} m={m} {integ}", flush=True)
+    sys_, x0 = lane_states(P, O, name, n)
+    full = O.IND_SALI | O.IND_GALI | O.IND_LYAP | O.IND_LD | O.IND_ENERGY
+    for ind, K in ((full, 7), (O.IND_LYAP | O.IND_ENERGY, 10), (O.IND_GALI, 3)):
+        if name == "quartic1" and not ind & O.IND_SALI:
+            continue  # two vectors: the kernels above
+        ms = m if ind & O.IND_GALI else 0
+        kw = dict(dt=0.05, T=15.0, indicators=ind, integrator=integ, renorm_every=K,
+                  escape_r2=4.0 if name == "hh" else 0.0)
+        if ms:
+            kw.update(gali_kmax=ms)
+        if ind & O.IND_SALI:
+            kw.update(early_exit=True, sali_threshold=0.02)
+        g = compare(env, sys_, x0, 33000, max(ms, 1), **kw)
+        if name == "hh" and ind & O.IND_SALI:
+            assert {O.ST_ESCAPED, O.ST_EXITED} <= set(g["status"].tolist())
