@@ -270,7 +270,7 @@ def checkpoint_flops_hh(N, m_s, n_l, energy, sali, energy_cost=14):
     return ck
 
 
-def flops_per_step_fput(N, m_s, n_l, ld, energy, sali, K):
+def flops_per_step_fput(N, m_s, n_l, ld, energy, sali, K, frame=False):
     """Algorithmic FP64 flops of one orbit-step of an FPU-beta chain of N
     masses between fixed walls (same conventions as flops_per_step): each
     force evaluation takes the N+1 spring elongations (1), forces
@@ -278,8 +278,10 @@ def flops_per_step_fput(N, m_s, n_l, ld, energy, sali, K):
     and the N+1 stiffnesses k + d (2 alpha + 3 beta d) (2 FMA) of the
     tridiagonal Hessian; a tangent kick scales the three diagonals by the
     kick's step (4 per mass, shared by all vectors) and applies them
-    (3 FMA per component)."""
-    M = m_s + n_l
+    (3 FMA per component).  frame: the SALI/GALI vectors are not integrated but
+    kept as coordinates in the Lyapunov set, a triangular 2N x 2N product
+    per vector and checkpoint."""
+    M = n_l if frame else m_s + n_l
     D = 2 * N
     force = 6 * (N + 1) + N + 4 * (N + 1)
     state = 3 * force + 4 * 2 * N + 3 * 2 * N
@@ -290,6 +292,8 @@ def flops_per_step_fput(N, m_s, n_l, ld, energy, sali, K):
         per += (2 * N - 1) + 1 + 2
     norm = 2 * D - 1 + D + 1
     ck = m_s * norm
+    if frame:
+        ck += m_s * D * (D + 1)
     if sali:
         ck += 2 * (D + 2 * D - 1)
     for j in range(n_l):
@@ -403,7 +407,8 @@ def bench_fput(args, P, chx, torch, dev):
         fps = model_flops_fput(N, 2 * N, N, K)
         full = [a.elapsed_time(b) for a, b, k in logs[N] if k == spl]
         ms = float(np.mean(full))
-        per_n[N] = dict(fps=fps, fps_exec=flops_per_step_fput(N, N, 2 * N, False, True, True, K),
+        per_n[N] = dict(fps=fps, fps_exec=flops_per_step_fput(N, N, 2 * N, False, True, True, K,
+                                                  frame=N == 8),
                         ms=ms, achieved=fps * n * spl / (ms * 1e-3), launches=len(full))
         # on every orbit: the exponents of a Hamiltonian flow sum to zero;
         # GALI_k lies in [0, 1] and does not grow with k
@@ -444,7 +449,7 @@ def bench_fput(args, P, chx, torch, dev):
                                 f"dt={dt}, T={T:g}",
                     "orbits": 2 * n, "steps_per_orbit": n_steps, "steps_per_launch": spl,
                     "per_N": {str(N): {"kernel": ("chx::fput_row_kernel<16, 3, 1, 1, true>" if N == 16
-                                                  else "chx::fput_rowpair_kernel<8>"),
+                                                  else "chx::fput_rowpair_kernel<8, true>"),
                                        "flops_per_orbit_step": v["fps"],
                                        "flops_per_orbit_step_executed": v["fps_exec"],
                                        "launch_ms": v["ms"],
@@ -855,7 +860,7 @@ def bench_gate(args, P, chx, torch, dev):
     roof_mlp = {"bound": "mfma", "achieved": mlp_fl / t_train / 1e12,
                 "peak": PEAK_BF16 / 1e12, "unit": "TFLOP/s",
                 "frac": mlp_fl / t_train / PEAK_BF16, "traffic": None,
-                "kernel": "chx::train_rows_kernel + chx::gemm_tile_kernel (training pass, all kernels)",
+                "kernel": "chx::train_rows_kernel + chx::batch_grads_kernel (training pass, all kernels)",
                 "flops_per_row_epoch": mlp_train_flops_per_row(),
                 "executed_flops_per_row_epoch": mlp_train_flops_per_row(True),
                 "time_basis": "whole training call"}
@@ -1227,7 +1232,7 @@ def bench_fig3(args, P, chx, torch, dev):
                     "per_N": rows, "kernel_s_N16_adaptive": kernel_s},
                 {"bound": "alu", "achieved": achieved / 1e12, "peak": PEAK_FP64 / 1e12,
                  "unit": "TFLOP/s", "frac": achieved / PEAK_FP64, "traffic": None,
-                 "kernel": "chx::fput_crow_rka_kernel<16, 4> (1000 orbits: a small fraction of "
+                 "kernel": "chx::fput_split_rka_kernel<16, 4> (1000 orbits: a small fraction of "
                            "the chip)", "flops_per_attempt": fpa,
                  "launch_ms": kernel_s * 1e3 / max(len(log), 1), "launches_timed": len(log)}, cpu)
 

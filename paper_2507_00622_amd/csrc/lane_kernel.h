@@ -167,7 +167,9 @@ struct LaneOrbit {
   // the two-lanes-per-orbit kernel holds them) and only the last
   // integrand is formed, for the next block.  6 instructions per root, one of
   // them v_rsq_f64, against 7.5 with an integrand per step: 8.5 million
-  // LD-only orbits, 2,000 steps, 35.2 -> 32.7 ms.
+  // LD-only orbits, 2,000 steps, 35.2 -> 32.7 ms.  The LD takes two roundings
+  // a block instead of one a step: its error against a compensated sum over
+  // the same trajectory goes from 1.6e-15 to 1.2e-15 (2-norm, T = 20).
   __device__ void block(const StepArgs &a, const StepCoef &k, int blk) {
     const bool do_ld = (a.ind & CHX_IND_LD) != 0;
     double sp = 0.0, sf = 0.0;
