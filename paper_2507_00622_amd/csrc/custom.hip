@@ -396,7 +396,7 @@ hipError_t custom_launch(void *handle, bool general, const Plan &pl, const StepA
   if (pl.o.integrator != CHX_INT_YOSHIDA4 && pl.M > 0) {
     const size_t per = custom_rk_lds_per_lane(general, pl.o.integrator == CHX_INT_DOP853_ADAPTIVE,
                                               pl.N, pl.M);
-    while (block > 64 && per * (size_t)block > 65536) block /= 2;
+    if (block > 64 && per * (size_t)block > 65536) block = 64;  // as LaneRKDispatch
     lds = per * (size_t)block;
     if (lds > 65536) return hipErrorInvalidValue;  // rejected by the plan already
   }

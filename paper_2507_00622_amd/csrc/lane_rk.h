@@ -522,7 +522,12 @@ struct LaneRKDispatch {
       // needed)
       constexpr int QW = RKOrbit<S, M, false, !ADAPT && hess_record<S, M>>::LDS_STAGE;
       const size_t per = M > 0 ? sizeof(double) * (12 * QW + (adaptive ? M * 2 * S::N : 0)) : 0;
-      while (block > 64 && per * (size_t)block > 65536) block /= 2;
+      // A block that has to shrink goes to one wavefront, not two: blocks of 128
+      // leave SIMDs idle while others hold two wavefronts.  Henon-Heiles, six
+      // vectors, 400 steps, blocks of 128 against 64: 40,000 orbits 4.81 / 3.02 ms,
+      // 212,700 11.1 / 10.9, 850,000 34.5 / 32.3; quartic N = 3, two vectors,
+      // 200 steps, 40,000 orbits 1.91 / 1.25.
+      if (block > 64 && per * (size_t)block > 65536) block = 64;
       const int64_t grid = (a.n + block - 1) / block;
       const size_t lds = per * (size_t)block;
       if constexpr (ADAPT) {
