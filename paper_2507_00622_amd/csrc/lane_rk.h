@@ -56,7 +56,8 @@ constexpr bool hess_record<SysHH, M> = M >= 3;
 // other's latency (held to 256 VGPRs, what spills is outside the step
 // loop).  212,700 orbits, six vectors, 1,000 steps: 31.5 ms with literal
 // coefficients and one vector a pass, 27.4 with the coefficients in
-// constant memory and the Hessian record, 26.3 with the pairs.
+// constant memory and the Hessian record, 26.3 with the pairs (25.5 in
+// blocks of 64).
 template <class S, int M>
 constexpr bool pair_passes = hess_record<S, M> && M >= 5;
 
