@@ -21,14 +21,18 @@ using namespace chx::host;
 namespace {
 
 // ---- autotune cache: GPU time per orbit-step of one pool kind at one
-// block size, for the whole device ---------------------------------------
+// block size, for the whole device.  A probe whose orbits fill the device
+// gives the time at the device's rate; one that does not gives an estimate
+// (probe_cost) under a key of its own, which only calls that do not fill the
+// device read, and only while there is no full one -------------------------
 std::mutex g_tune_mu;
 std::map<std::string, double> g_tune;
 std::string g_tune_path;  // cache file last read ("" = none)
 
-std::string tune_key(int kind, int threads, uint32_t ind) {
+std::string tune_key(int kind, int threads, uint32_t ind, bool full) {
   char b[96];
-  snprintf(b, sizeof b, "gfx950/kind%d/threads%d/ind%u", kind, threads, ind);
+  snprintf(b, sizeof b, "gfx950/kind%d%s/threads%d/ind%u", kind, full ? "" : "/part", threads,
+           ind);
   return b;
 }
 
@@ -63,9 +67,13 @@ struct PoolBuf {
 };
 
 // Probe: one short launch of the persistent kernel on a copy of up to `m`
-// orbits of pool `src`; returns seconds per orbit-step.
-chx_status probe_cost(const Pool &src, const Plan &pl, int threads, int blocks, hipStream_t s,
-                      double *cost) {
+// orbits of pool `src`; returns seconds per orbit-step of a device filled with
+// at least `fill` orbits, one wavefront per SIMD.  Fewer orbits than that take
+// as long as `fill` of them, so the time is shared by `fill`; between that
+// and the slots of the device (three wavefronts per SIMD) the time grows
+// by less than the orbits, and the estimate is at most three times the rate.
+chx_status probe_cost(const Pool &src, const Plan &pl, int threads, int blocks, int64_t fill,
+                      hipStream_t s, double *cost) {
   const int64_t m = src.a.n;
   const int64_t Pm = ((m + 63) / 64) * 64;
   const int D = pl.D, M = pl.M;
@@ -137,7 +145,7 @@ chx_status probe_cost(const Pool &src, const Plan &pl, int threads, int blocks, 
   if (e0) (void)hipEventDestroy(e0);
   if (e1) (void)hipEventDestroy(e1);
   if (he != hipSuccess) return dev_fail(he, "autotune probe");
-  *cost = (double)ms * 1e-3 / ((double)m * (double)b.budget);
+  *cost = (double)ms * 1e-3 / ((double)(m > fill ? m : fill) * (double)b.budget);
   return CHX_OK;
 }
 
@@ -274,26 +282,29 @@ extern "C" chx_status chx_integrate_batched(const chx_batch_item *items, int32_t
     double total = 0.0;
     std::vector<double> cost(n_items, 0.0);
     for (int i = 0; i < n_items; ++i) {
-      const std::string key = tune_key(kinds[i], threads, opt->indicators);
+      const int64_t slots = waves * 64 / pool_slot_width(kinds[i]);
+      const bool full = ens[i]->n_active >= slots;
       double c = 0.0;
       {
         std::lock_guard<std::mutex> g(g_tune_mu);
         tune_load();
-        auto it = g_tune.find(key);
+        auto it = g_tune.find(tune_key(kinds[i], threads, opt->indicators, true));
+        if (it == g_tune.end() && !full)
+          it = g_tune.find(tune_key(kinds[i], threads, opt->indicators, false));
         if (it != g_tune.end()) c = it->second;
       }
       if (c <= 0.0 && ens[i]->n_active > 0) {
         from_cache = 0;
-        const int64_t slots = waves * 64 / pool_slot_width(kinds[i]);
         Pool probe = b.pool[i];
-        probe.a.n = ens[i]->n_active < slots ? ens[i]->n_active : slots;
-        st = probe_cost(probe, plans[i], threads, blocks, bs, &c);
+        probe.a.n = full ? slots : ens[i]->n_active;
+        st = probe_cost(probe, plans[i], threads, blocks,
+                        (int64_t)ncu * 4 * 64 / pool_slot_width(kinds[i]), bs, &c);
         if (st) {
           cleanup();
           return st;
         }
         std::lock_guard<std::mutex> g(g_tune_mu);
-        tune_store(key, c);
+        tune_store(tune_key(kinds[i], threads, opt->indicators, full), c);
       }
       cost[i] = c;
       total += c * (double)ens[i]->n_active * (double)plans[i].n_total;
