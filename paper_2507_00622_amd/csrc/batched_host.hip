@@ -356,15 +356,20 @@ extern "C" chx_status chx_integrate_batched(const chx_batch_item *items, int32_t
     }
     b.split[n_items] = waves;
   }
-  // Steps per launch: at most about 200 ms of GPU time, and at most 1/32 of
-  // the longest run of a system with a lane per orbit.  There a slot that
-  // exits early refills by itself, so orbits integrated to the end one after
-  // another end scattered over wavefronts that are mostly idle; short turns
-  // carry all orbits forward together and pack them anew (262,144
-  // Henon-Heiles, 65,536 quartic and 16,384 FPU orbits to T = 400: 130 ms at
-  // 51,260 steps per launch, 98 at 4,000, 93 at 2,000, 92 at 1,250, 106 at
-  // 500).  Rows refill four to a wavefront and move more state per turn: FPU
-  // chains alone take 21 ms in one turn, 26 in turns of 1/32.
+  // Steps per launch: at most about 200 ms of GPU time.  Where orbits may exit
+  // early, systems with a lane per orbit carry most of the work and their runs
+  // are long, at most 1/32 of the longest run (and no fewer than 1,000 steps): a slot
+  // refills by itself when its orbit exits, so in one long turn the orbits
+  // integrated to the end one after another end scattered over wavefronts that
+  // are mostly idle; short turns carry all orbits forward together and pack
+  // them anew.  262,144 Henon-Heiles, 65,536 quartic and 16,384 FPU orbits, ms in
+  // one turn / in turns of 1,000: 40,000 steps 122 / 90, 32,000 92 / 74, 28,000
+  // 77 / 65, 24,000 61 / 56; below, few orbits exit before the end and a turn
+  // costs more than it packs: at 1,250 a turn 20,000 40 / 44, 10,000 22 / 23.  Henon-Heiles
+  // alone without early exit, 40,000 steps, 31 / 38.  The state of 2^20
+  // orbits takes 1/10 of the time at 1,000 steps a turn, and 85 % at 30.
+  // Rows refill four to a wavefront and move more state per turn: FPU chains alone
+  // take 21 ms in one turn, 24 in turns of 1,250.
   const int K = plans[0].K;
   int64_t budget = opt->steps_per_launch;
   if (budget <= 0) {
@@ -374,10 +379,19 @@ extern "C" chx_status chx_integrate_batched(const chx_batch_item *items, int32_t
       worst = fmax(worst, best_cost[i] * slots);
     }
     budget = worst > 0.0 ? (int64_t)(0.2 / worst) : 100000;
-    int64_t longest = 0;
-    for (int i = 0; i < n_items; ++i)
-      if (pool_slot_width(kinds[i]) == 1 && plans[i].n_total > longest) longest = plans[i].n_total;
-    if (longest > 0 && budget > longest / 32) budget = longest / 32;
+    double work[2] = {0.0, 0.0};  // of the pools with a row per orbit, a lane per orbit
+    int64_t longest = 0, longest_lane = 0;
+    for (int i = 0; i < n_items; ++i) {
+      if (ens[i]->n_active == 0) continue;
+      const bool lane = pool_slot_width(kinds[i]) == 1;
+      work[lane] += best_cost[i] * (double)ens[i]->n_active * (double)plans[i].n_total;
+      if (plans[i].n_total > longest) longest = plans[i].n_total;
+      if (lane && plans[i].n_total > longest_lane) longest_lane = plans[i].n_total;
+    }
+    if (opt->early_exit && longest_lane >= 24000 && work[1] >= work[0]) {
+      const int64_t turn = longest / 32 > 1000 ? longest / 32 : 1000;
+      if (budget > turn) budget = turn;
+    }
   }
   budget = (budget / K) * K;
   if (budget < K) budget = K;
