@@ -162,14 +162,13 @@ struct LaneOrbit {
     kick_state(k.hk0);  // p at the step endpoint
   }
   // blk whole steps from one checkpoint to the next.  The LD's trapezoid sum
-  // over them is dt (g_1 + ... + g_blk) + dt/2 (g_0 - g_blk): inside the block
-  // each root joins a running sum (the momenta's and the force's apart, as
-  // the two-lanes-per-orbit kernel holds them) and only the last
+  // over them is dt/2 (2 (g_1 + ... + g_{blk-1}) + (g_0 + g_blk)): inside the
+  // block each root joins a running sum (the momenta's and the force's apart,
+  // as the two-lanes-per-orbit kernel holds them) and only the last
   // integrand is formed, for the next block.  6 instructions per root, one of
   // them v_rsq_f64, against 7.5 with an integrand per step: 8.5 million
-  // LD-only orbits, 2,000 steps, 35.2 -> 32.7 ms.  The LD takes two roundings
-  // a block instead of one a step: its error against a compensated sum over
-  // the same trajectory goes from 1.6e-15 to 1.2e-15 (2-norm, T = 20).
+  // LD-only orbits, 2,000 steps, 35.2 -> 32.7 ms.  The LD is rounded once a
+  // block, with one step per block as it is with an integrand per step.
   __device__ void block(const StepArgs &a, const StepCoef &k, int blk) {
     const bool do_ld = (a.ind & CHX_IND_LD) != 0;
     double sp = 0.0, sf = 0.0;
@@ -199,15 +198,13 @@ struct LaneOrbit {
         ld_add(a, x[N + r], gp);
         ld_add(a, F[r], gf);
       }
-      ld_block(a, k, sp + sf, gp + gf);
+      ld_block(k, sp + sf, gp + gf);
     }
     kick_vectors(a, k.hk0);
   }
   // s: the integrands of the block's inner endpoints; g: of its last
-  __device__ __forceinline__ void ld_block(const StepArgs &a, const StepCoef &k, double s,
-                                           double g) {
-    ld = __builtin_fma(a.dt, s + g, ld);
-    ld = __builtin_fma(k.hdt, gprev - g, ld);
+  __device__ __forceinline__ void ld_block(const StepCoef &k, double s, double g) {
+    ld = __builtin_fma(k.hdt, __builtin_fma(2.0, s, gprev + g), ld);
     gprev = g;
   }
 

@@ -75,7 +75,7 @@ struct PairOrbit : LaneOrbit<S, 1, false, -1> {
       double g = 0.0;
 #pragma unroll
       for (int r = 0; r < N; ++r) add_sqrt_ld(v == 0 ? x[N + r] : F[r], g);
-      this->ld_block(a, k, sum + other(sum), g + other(g));
+      this->ld_block(k, sum + other(sum), g + other(g));
     }
     this->kick_vectors(a, k.hk0);
   }

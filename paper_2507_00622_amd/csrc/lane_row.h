@@ -198,7 +198,7 @@ struct RowOrbit : LaneOrbit<S, 1, false, -1> {
       double g = 0.0;
 #pragma unroll
       for (int r = 0; r < N; ++r) add_sqrt_ld(momenta ? x[N + r] : F[r], g);
-      this->ld_block(a, k, sum + other(sum), g + other(g));
+      this->ld_block(k, sum + other(sum), g + other(g));
     }
     this->kick_vectors(a, k.hk0);
   }
