@@ -375,7 +375,10 @@ extern "C" chx_status chx_integrate_batched(const chx_batch_item *items, int32_t
   if (budget <= 0) {
     double worst = 0.0;
     for (int i = 0; i < n_items; ++i) {
-      const double slots = (double)waves * 64.0 / pool_slot_width(kinds[i]);
+      if (ens[i]->n_active == 0) continue;
+      // a step of fewer orbits takes no less than one of a wavefront per SIMD
+      const int busy = waves > 4 * ncu ? waves : 4 * ncu;
+      const double slots = (double)busy * 64.0 / pool_slot_width(kinds[i]);
       worst = fmax(worst, best_cost[i] * slots);
     }
     budget = worst > 0.0 ? (int64_t)(0.2 / worst) : 100000;

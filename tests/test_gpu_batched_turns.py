@@ -92,3 +92,12 @@ def test_turns_only_where_orbits_exit_early(env):
     for a, b in zip(outs, plain(env, items)):
         for k in a:
             assert np.array_equal(a[k], b[k], equal_nan=True), k
+
+
+def test_turn_time_of_few_orbits(env):
+    torch, P, O = env
+    print("case: a turn of few orbits takes about 200 ms at most", flush=True)
+    _, st = run(env, [fput(P, O, 16, 2000)])
+    # a step takes at least as long as one with a wavefront on every SIMD
+    rows = 4 * torch.cuda.get_device_properties(0).multi_processor_count * 4
+    assert st["steps_per_launch"] * st["cost_ps"][0] * 1e-12 * rows < 0.201
