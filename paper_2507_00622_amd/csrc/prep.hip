@@ -253,12 +253,13 @@ __global__ void gali_lane_kernel(StepArgs a, OutArgs o, int N) {
 // them (no barrier).  A block's 16 orbits share the 128-byte lines of the
 // vectors' columns.  65,536 FPU chains of 16 masses, GALI_2..16: one lane
 // per orbit with its copies in global memory took 6.7 ms of a 26.5 ms call,
-// which now takes 19.5 ms.
+// which now takes 19.5 ms.  Rows stride over the orbits, GALI_ROW_BLOCKS blocks at
+// most: 16 threads an orbit would pass the 2^32 - 1 threads of a launch at
+// 2^28 orbits, which fit the memory (user systems of 5..8 degrees of freedom).
+constexpr int64_t GALI_ROW_BLOCKS = 65536;
 template <int CPL>
-__global__ void gali_row_kernel(StepArgs a, OutArgs o, int N) {
+__device__ __forceinline__ void gali_row(const StepArgs &a, const OutArgs &o, int N, int64_t i) {
   using fputrow::row_sum;
-  const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 4;
-  if (i >= a.n) return;  // whole rows leave
   const int lane = threadIdx.x & 15;
   const int D = 2 * N, km = o.gali_kmax, T = blockDim.x;
   const int64_t P = a.pitch;
@@ -301,6 +302,12 @@ __global__ void gali_row_kernel(StepArgs a, OutArgs o, int N) {
     prod *= rj;
     if (v >= 1 && lane == 0) g[v - 1] = prod;
   }
+}
+template <int CPL>
+__global__ void gali_row_kernel(StepArgs a, OutArgs o, int N) {
+  const int64_t first = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 4;
+  const int64_t rows = ((int64_t)gridDim.x * blockDim.x) >> 4;
+  for (int64_t i = first; i < a.n; i += rows) gali_row<CPL>(a, o, N, i);  // whole rows leave
 }
 
 __global__ void masked_fill_kernel(const double *x0, const uint8_t *mask, int64_t n, int N,
@@ -576,7 +583,9 @@ hipError_t launch_finalize(const StepArgs &a, const OutArgs &oa, int ndof, hipSt
     const size_t per = sizeof(double) * oa.gali_kmax * (rows ? (D > 16 ? 2 : 1) : D);
     int tpb = TPB;
     while (tpb > 64 && per * tpb > 65536) tpb /= 2;
-    const dim3 grid(blocks_for(rows ? a.n * 16 : a.n, tpb));
+    const int64_t row_blocks = (a.n * 16 + tpb - 1) / tpb;
+    const dim3 grid(!rows ? blocks_for(a.n, tpb)
+                          : (unsigned)(row_blocks < GALI_ROW_BLOCKS ? row_blocks : GALI_ROW_BLOCKS));
     if (!rows)
       hipLaunchKernelGGL(gali_lane_kernel, grid, dim3(tpb), per * tpb, s, a, oa, ndof);
     else if (D > 16)
