@@ -110,11 +110,15 @@ chx_status check_system(const chx_system *sys) {
 // Whether the SALI/GALI set is kept as coordinates in the frame of the full
 // Lyapunov set (StepArgs::frame) instead of being integrated: FPU chains of
 // N = 8 on the row-pair kernel.
-// The coordinates lose what the frame loses: its vectors come out of the
-// Gram-Schmidt orthonormal to 1e-16 times the stretching ratio of one
-// checkpoint interval.  With the step resolving the motion (rate times step
-// below about 0.3) K = 16 steps keep that below 1e-12; longer intervals
-// integrate the set.
+// The frame comes out of the Gram-Schmidt orthonormal to 1e-16 times the
+// condition of one checkpoint interval's map: at K = 16 about 1e-14 where the
+// step resolves the motion (condition below 100 at rates of 1 and steps of 0.02)
+// and 1e-12 for rates of 0.3 per step.  That enters where the coordinates are
+// measured and does not add up, and a nearly singular map has cost the
+// measured vectors the same directions: SALI and GALI are as close to
+// extended-precision ones as those of the integrated set, also at steps of 0.5 and
+// in chains that blow up within an interval (condition up to 1e35).  Longer
+// intervals than those compared, K = 16, integrate the set.
 // N = 16 was tried: the product with R costs 528 of the 1,920 FMAs it saves per
 // checkpoint and lengthens the pivots' chain (20.3 against 19.5 to 20.4 ms
 // for 65,536 chains and 500 steps).  So were the lane kernels (Henon-Heiles
