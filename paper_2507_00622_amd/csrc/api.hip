@@ -20,7 +20,7 @@ namespace chx {
 hipError_t launch_fput_crow_rk(int ndof, int M, bool adaptive, const StepArgs &a,
                                hipStream_t s);
 // FPU chains of small ensembles, a row per vector (fput_split*.hip)
-bool fput_split_wanted(const StepArgs &a);
+bool fput_split_wanted(bool rk, const StepArgs &a);
 hipError_t launch_fput_split(int ndof, const StepArgs &a, hipStream_t s);
 hipError_t launch_fput_split_rk(int ndof, const StepArgs &a, hipStream_t s);
 hipError_t launch_fput_split_rka(int ndof, const StepArgs &a, hipStream_t s);
@@ -113,7 +113,7 @@ chx_status check_system(const chx_system *sys) {
 // The frame comes out of the Gram-Schmidt orthonormal to 1e-16 times the
 // condition of one checkpoint interval's map: at K = 16 about 1e-14 where the
 // step resolves the motion (condition below 100 at rates of 1 and steps of 0.02)
-// and 1e-12 for rates of 0.3 per step.  That enters where the coordinates are
+// and 1.5e-12 for rates of 0.3 per step.  That enters where the coordinates are
 // measured and does not add up, and a nearly singular map has cost the
 // measured vectors the same directions: SALI and GALI are as close to
 // extended-precision ones as those of the integrated set, also at steps of 0.5 and
@@ -423,7 +423,7 @@ chx_status advance(chx_ensemble *e, int64_t s_end) {
                           ? custom_launch(e->custom, e->kind == CHX_SYS_CUSTOM_GENERAL, pl, a,
                                           e->block, e->stream)
                       : (e->kind == CHX_SYS_FPUT)
-                          ? (fput_split_wanted(a)
+                          ? (fput_split_wanted(pl.o.integrator != CHX_INT_YOSHIDA4, a)
                                  ? (pl.o.integrator == CHX_INT_YOSHIDA4
                                         ? launch_fput_split(pl.N, a, e->stream)
                                     : pl.o.integrator == CHX_INT_DOP853

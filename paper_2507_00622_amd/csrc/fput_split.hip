@@ -20,9 +20,12 @@ hipError_t go(const StepArgs &a, hipStream_t s) {
 // T = 20: n = 1,000 2.79 / 1.59 ms, 2,048 2.94 / 2.30, 4,096 3.09 / 3.40;
 // Yoshida-4, 4,000 steps: 2.08 / 1.32, 2.23 / 2.12, 2.29 / 3.53; N = 16, two
 // vectors, adaptive: 1.63 / 1.23, 1.61 / 1.25, 1.78 / 1.88; Yoshida-4: 1.37 /
-// 1.21, 1.40 / 1.23, 1.59 / 2.00.
-bool fput_split_wanted(const StepArgs &a) {
-  return a.n_l == 0 && a.m_s >= 2 && a.m_s <= 4 && a.n <= 2048;
+// 1.21, 1.40 / 1.23, 1.59 / 2.00.  With three vectors the fourth row repeats one,
+// and Yoshida-4 stops at one wavefront per SIMD (1,200 steps, microseconds: N = 3,
+// n = 1,500 587 / 660, 2,040 590 / 674; N = 6, 640 / 692, 644 / 686).
+bool fput_split_wanted(bool rk, const StepArgs &a) {
+  if (a.n_l != 0 || a.m_s < 2 || a.m_s > 4) return false;
+  return a.n <= (a.m_s == 3 && !rk ? 1024 : 2048);
 }
 
 hipError_t launch_fput_split(int ndof, const StepArgs &a, hipStream_t s) {

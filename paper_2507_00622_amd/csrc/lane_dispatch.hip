@@ -25,9 +25,9 @@ hipError_t launch_lane_rk_harmonic2(int M, bool adaptive, const StepArgs &a, int
 hipError_t launch_lane_rk_harmonic3(int M, bool adaptive, const StepArgs &a, int block,
                             hipStream_t s);
 hipError_t launch_lane_rk_dp(int M, bool adaptive, const StepArgs &a, int block, hipStream_t s);
-bool lane_row_wanted(bool rk, const StepArgs &a);
+bool lane_row_wanted(int ndof, bool rk, const StepArgs &a);
 hipError_t launch_lane_row(int sys, int ndof, bool rk, const StepArgs &a, hipStream_t s);
-bool lane_pair_wanted(const StepArgs &a);
+bool lane_pair_wanted(int ndof, const StepArgs &a);
 hipError_t launch_lane_pair(int sys, int ndof, const StepArgs &a, hipStream_t s);
 bool lane_quad_wanted(int sys, const StepArgs &a);
 hipError_t launch_lane_quad(int sys, int ndof, bool adaptive, const StepArgs &a, hipStream_t s);
@@ -51,8 +51,8 @@ hipError_t launch_lane(int sys, int ndof, int M, const StepArgs &a, int block,
       sys == CHX_SYS_CUSTOM_GENERAL)
     return hipErrorInvalidValue;
   if (a.n == 0) return hipSuccess;
-  if (lane_row_wanted(false, a)) return launch_lane_row(sys, ndof, false, a, s);
-  if (lane_pair_wanted(a)) return launch_lane_pair(sys, ndof, a, s);
+  if (lane_row_wanted(ndof, false, a)) return launch_lane_row(sys, ndof, false, a, s);
+  if (lane_pair_wanted(ndof, a)) return launch_lane_pair(sys, ndof, a, s);
   switch (sys) {
   case SYS_HH: return launch_lane_hh(M, a, block, s);
   case SYS_QUARTIC:
@@ -73,7 +73,7 @@ hipError_t launch_lane_rk(int sys, int ndof, int M, bool adaptive, const StepArg
                           int block, hipStream_t s) {
   if (!lane_supported(sys, ndof, M)) return hipErrorInvalidValue;
   if (a.n == 0) return hipSuccess;
-  if (!adaptive && lane_row_wanted(true, a)) return launch_lane_row(sys, ndof, true, a, s);
+  if (!adaptive && lane_row_wanted(ndof, true, a)) return launch_lane_row(sys, ndof, true, a, s);
   if (lane_quad_wanted(sys, a)) return launch_lane_quad(sys, ndof, adaptive, a, s);
   switch (sys) {
   case SYS_HH: return launch_lane_rk_hh(M, adaptive, a, block, s);

@@ -44,8 +44,15 @@ hipError_t dispatch(int sys, int ndof, const StepArgs &a, hipStream_t s) {
 //              quartic N = 3, M = 3        3.93  1.30   3.50  2.20   3.55  4.16
 //              quartic N = 3, M = 12       12.1  2.22   11.9  2.28   11.8  4.28
 //              double pendulum, M = 6      13.8  4.01   14.0  7.16   13.9  13.8
-bool lane_row_wanted(bool rk, const StepArgs &a) {
+// A checkpoint's pivots go through the row one after another, which a Yoshida-4
+// row makes up for between checkpoints if they are K (N - 1) >= 5 steps and
+// degrees of freedom apart.  One lane against a row, 4,000 orbits, 1,000 steps
+// (microseconds): M = 3, Henon-Heiles K = 1 723 / 914, 2 527 / 598, 4 420 / 433,
+// harmonic N = 3 K = 1 743 / 841, 2 528 / 558; M = 4 (400 steps), quartic N = 1
+// K = 1 373 / 506, 5 251 / 265, 10 234 / 233; Henon-Heiles M = 6 K = 5 353 / 318.
+bool lane_row_wanted(int ndof, bool rk, const StepArgs &a) {
   const int M = a.m_s + a.n_l;
+  if (!rk && (int64_t)a.K * (ndof - 1) < 5) return false;
   if (M < 3 || M > 12 || ((a.ind & CHX_IND_LD) && a.ld_p != 0.5)) return false;
   return a.n <= (rk ? 8192 : 4096);
 }

@@ -142,7 +142,7 @@ def test_lane_per_vector_against_one(env, name, m, n_l, integ):
         pytest.skip("no Yoshida-4 for the double pendulum")
     print(f"case: a lane per vector against one lane, {name} {m}+{n_l} {integ}", flush=True)
     ind = O.IND_SALI | O.IND_GALI | O.IND_LD | O.IND_ENERGY | (O.IND_LYAP if n_l else 0)
-    for K in (1, 10):
+    for K in (1, 5, 10):  # Yoshida-4 rows need K (N - 1) >= 5
         compare(env, name, m, ROW if integ == "yoshida4" else ROW_RK, dt=0.05, T=12.0,
                 integrator=integ, indicators=ind, renorm_every=K, gali_kmax=m, n_lyap=n_l,
                 escape_r2=4.0 if name == "hh" else 0.0)
