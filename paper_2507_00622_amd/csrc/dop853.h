@@ -121,6 +121,27 @@ __device__ __forceinline__ Coef coef() {
   asm volatile("" : "+s"(p));
   return p;
 }
+// A fixed step of the state alone has one pass a step and few values beside the
+// literals, which then cost less than the loads' latency: FPU chains (3,000, 80
+// steps, LD) 0.235 ms with literals, 0.261 with the table; one degree of
+// freedom (quartic, 8,000, 1,000 steps, LD) 0.974 / 1.076; two (Henon-Heiles,
+// 64,000) 1.72 / 1.77.  With three, and in the adaptive solver, the table is ahead.
+struct Literals {};
+template <bool LITERALS>
+__device__ __forceinline__ auto pass_coef() {
+  if constexpr (LITERALS)
+    return Literals{};
+  else
+    return coef();
+}
+template <int AT>
+__device__ __forceinline__ double coef_of(Coef cf, double) {
+  return cf[AT];
+}
+template <int AT>
+__device__ __forceinline__ double coef_of(Literals, double value) {
+  return value;
+}
 
 template <int I, int E, class Fn>
 __device__ __forceinline__ void static_for(Fn &&f) {
@@ -131,12 +152,13 @@ __device__ __forceinline__ void static_for(Fn &&f) {
 }
 
 // sum_{j<I} A[I][j] k[j][c] over the non-zero entries, in order of j
-template <int I, int D>
-__device__ __forceinline__ double stage_sum(Coef cf, const double (&k)[12][D], int c) {
+template <int I, class CF, int D>
+__device__ __forceinline__ double stage_sum(CF cf, const double (&k)[12][D], int c) {
   double s = 0.0;
   static_for<0, I>([&](auto jc) {
     constexpr int J = decltype(jc)::value;
-    if constexpr (A[I][J] != 0.0) s = __builtin_fma(cf[nonzero_before(I, J)], k[J][c], s);
+    if constexpr (A[I][J] != 0.0) 
+      s = __builtin_fma(coef_of<nonzero_before(I, J)>(cf, A[I][J]), k[J][c], s);
   });
   return s;
 }
@@ -150,12 +172,13 @@ __device__ __forceinline__ double err5_sum(Coef cf, const double (&k)[12][D], in
   });
   return s;
 }
-template <int D>
-__device__ __forceinline__ double final_sum(Coef cf, const double (&k)[12][D], int c) {
+template <class CF, int D>
+__device__ __forceinline__ double final_sum(CF cf, const double (&k)[12][D], int c) {
   double s = 0.0;
   static_for<0, 12>([&](auto jc) {
     constexpr int J = decltype(jc)::value;
-    if constexpr (B[J] != 0.0) s = __builtin_fma(cf[AT_B + weights_before(B, J)], k[J][c], s);
+    if constexpr (B[J] != 0.0) 
+      s = __builtin_fma(coef_of<AT_B + weights_before(B, J)>(cf, B[J]), k[J][c], s);
   });
   return s;
 }

@@ -38,7 +38,8 @@ struct CRowRK : CRowOrbit<N, M> {
 
   // the state's 12 stages: k = h f at Y = x + sum a_ij k_j; g += the LD
   // integrand of this lane's components at the weighted stages
-  __device__ __forceinline__ void state_pass(const StepArgs &a, dop853::Coef cf, double h, bool do_ld,
+  template <class CF>
+  __device__ __forceinline__ void state_pass(const StepArgs &a, CF cf, double h, bool do_ld,
                                              double (&kq)[12][1], double (&kp)[12][1],
                                              double &g) {
     dop853::static_for<0, 12>([&](auto ic) {
@@ -79,7 +80,7 @@ struct CRowRK : CRowOrbit<N, M> {
   // one fixed DOP853 step of size h
   __device__ __forceinline__ void rk_step(const StepArgs &a, double h, bool do_ld) {
     {
-      const dop853::Coef cf = dop853::coef();
+      const auto cf = dop853::pass_coef<M == 0>();
       double kq[12][1], kp[12][1], g = 0.0;
       state_pass(a, cf, h, do_ld, kq, kp, g);
       q += dop853::final_sum(cf, kq, 0);

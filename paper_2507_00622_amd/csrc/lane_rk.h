@@ -138,8 +138,8 @@ struct RKOrbit : LaneOrbit<S, M, GP, -1> {
 
   // Stage I of the state: Y = x + sum_j a_Ij k_j; its LDS record; the LD
   // integrand sum |dY/dt|^p at weighted stages into g; k_I = h f(Y).
-  template <int I>
-  __device__ __forceinline__ void state_stage(const StepArgs &a, dop853::Coef cf, double h, bool do_ld,
+  template <int I, class CF>
+  __device__ __forceinline__ void state_stage(const StepArgs &a, CF cf, double h, bool do_ld,
                                               double *qs, int stride, double (&k)[12][D],
                                               double &g) {
     double Y[D], f[D];
@@ -252,7 +252,7 @@ struct RKOrbit : LaneOrbit<S, M, GP, -1> {
       return;
     }
     {
-      const dop853::Coef cf = dop853::coef();
+      const auto cf = dop853::pass_coef<M == 0 && !GEN && N <= 2>();
       double k[12][D];  // h f(Y_i) of the state
       double g = 0.0;   // sum_i b_i (LD integrand at stage i)
       dop853::static_for<0, 12>([&](auto ic) {
