@@ -212,7 +212,12 @@ typedef struct {
                              stream 0 */
   double escape_r2;       /* 0 = off */
   uint32_t flags;         /* CHX_PTR_DEVICE */
-  int32_t block_size;     /* threads per block for the lane kernel; 0 -> tuned */
+  int32_t block_size;     /* threads per block for the lane kernel; 0 -> tuned.
+                             Results do not depend on it.  Ignored by the FPU
+                             chains and by small ensembles of the built-in
+                             lane systems (up to 4,096 to 32,768 active orbits by
+                             integrator and indicators), whose kernels fix their
+                             blocks */
   void *stream;           /* hipStream_t for CHX_PTR_DEVICE calls */
   int32_t integrator;     /* CHX_INT_*; 0 -> Yoshida-4.  The batched form and
                              the convenience calls use Yoshida-4 */
@@ -382,7 +387,8 @@ chx_status chx_ensemble_subset(chx_ensemble *e, const uint8_t *keep, chx_ensembl
  * threads per block and the steps per launch; 0 lets the autotuner choose
  * (it times short probe launches on copies of the ensembles, per system and
  * block size; timings are cached for the process and, if the environment
- * variable CHX_AUTOTUNE_CACHE names a file, in that file).  Results per
+ * variable CHX_AUTOTUNE_CACHE names a file, in that file; those of ensembles
+ * that do not fill the device serve only such calls).  Results per
  * item as for chx_integrate_ensemble.  stats may be NULL. */
 typedef struct {
   chx_system sys;

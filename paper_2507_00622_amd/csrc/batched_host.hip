@@ -363,7 +363,7 @@ extern "C" chx_status chx_integrate_batched(const chx_batch_item *items, int32_t
   // integrated to the end one after another end scattered over wavefronts that
   // are mostly idle; short turns carry all orbits forward together and pack
   // them anew.  262,144 Henon-Heiles, 65,536 quartic and 16,384 FPU orbits, ms in
-  // one turn / in turns of 1,000: 40,000 steps 122 / 90, 32,000 92 / 74, 28,000
+  // one turn / in turns by this rule: 40,000 steps 122 / 91, 32,000 92 / 74, 28,000
   // 77 / 65, 24,000 61 / 56; below, few orbits exit before the end and a turn
   // costs more than it packs: at 1,250 a turn 20,000 40 / 44, 10,000 22 / 23.  Henon-Heiles
   // alone without early exit, 40,000 steps, 31 / 38.  The state of 2^20
